@@ -3,17 +3,16 @@
 // global permutation with the top-level twiddle, LocalFFT in input layout),
 // all inside ONE persistent kernel launch.
 //
-// Work is cut into tasks: one column tile of Phase I, one 64-row tile of
-// Phase II, one column tile of Phase III of one transform ("jobs" are the
-// (transform, phase) pairs), and, for transforms of at most 2^12 items, the
-// whole transform in one workgroup (its three phases separated by workgroup
-// barriers, the intermediates staying in L2).  A resident workgroup claims
-// the next task number from an atomic ticket counter.  A Phase II task waits
-// until every tile of its transform's Phase I job is done, a Phase III task
-// for Phase II, on per-job completion counters: the producer writes those
-// tiles with device-coherent stores, waits for them to complete and then
-// increments the counter; the consumer reads the counter with a device-scope
-// acquire load (which also drops stale cache lines) before touching the data.
+// Work is cut into tasks: up to 2^13 items of whole transforms of one size
+// of at most 2^13 items, a whole transform of 2^14 items, or, for larger
+// ones, one 2^14-item tile of the first or of the second column pass of one
+// transform (tile.h; "jobs" are the (transform, pass) pairs).  A resident
+// workgroup claims the next task number from an atomic ticket counter.  A
+// pass-B task waits until every tile of its transform's pass A is done, on a
+// per-job completion counter: the producer writes those tiles, waits for the
+// stores to complete and then increments the counter; the consumer reads the
+// counter and takes a device-scope acquire fence (which also drops stale
+// cache lines) before touching the data.
 //
 // Forward progress: tickets are claimed in increasing order by workgroups
 // that are already running, and a task only waits for jobs whose tasks all
@@ -39,18 +38,17 @@
 #include <vector>
 
 #include "paco.h"
-#include "middle_dev.h"
-#include "stages.h"
+#include "tile.h"
 
 namespace paco {
 namespace {
 
-constexpr int kBT = 256;             // threads per workgroup of the persistent kernel
+constexpr int kBT = 512;             // threads per workgroup of the persistent kernel
 constexpr int kBatchMinLog2 = 2;     // N >= 4 (N1, N2 >= 2)
-constexpr int kBatchMaxLog2 = 20;    // local lengths <= 2^10
-constexpr int kSmallMaxLog2 = 12;    // whole transform inside one workgroup
-constexpr int kBigMinLocal = 6;      // Phase II tiles need N1, N2 >= 64
-constexpr int kBigMaxLocal = 10;
+constexpr int kBatchMaxLog2 = 20;    // pass lengths <= 2^10
+constexpr int kChipMaxLog2 = 14;     // whole transform inside one workgroup
+constexpr int kTileLog2 = 14;        // items of a pass tile: 32 per thread, in two groups
+constexpr int kPassMin = 7, kPassMax = 10;
 constexpr uint32_t kSpinLimit = 1u << 22;
 // s_waitcnt operand that waits for vmcnt = 0 only (gfx9 encoding: vmcnt in
 // bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima)
@@ -61,26 +59,21 @@ constexpr int kHwRegXccId = 20 | (0 << 6) | ((4 - 1) << 11);
 constexpr int kMaxQueues = 16;
 constexpr int kTicketStride = 64;  // counters 256 bytes apart
 
-enum : int32_t { kSmall = 0, kP1 = 1, kP2 = 2, kP3 = 3 };
+enum : int32_t { kSmall = 0, kOne = 1, kPassA = 2, kPassB = 3 };
 
 struct alignas(8) BatchJob {
-    int64_t base;            // first item of the transform in in / out / workspace
-    int32_t kind;            // kSmall, kP1, kP2, kP3
-    int32_t l1, l2, t;       // N1 = 2^l1, N2 = 2^l2, b = 2^t
-    int32_t v1, v3;          // tile variants of Phase I / Phase III
+    int64_t base;            // first item of the transform in in / out / workspace; kSmall: first entry of members
+    int32_t kind;
+    int32_t l1, l2;          // the passes' lengths 2^l1 (A), 2^l2 (B); kSmall: 2^l1 points
+    int32_t count;           // kSmall: transforms of the task
     int32_t dep, dep_tiles;  // job this one waits for (-1: none) and its tile count
     int32_t ntiles;          // tasks of this job
-    int32_t tab;             // Phase-II table set of the transform size
+    int32_t tab;             // table set of the transform size (kOne, kPassB)
     int32_t signal;          // 1: a later job waits for this one
-    int32_t pad;
+    int32_t pad[3];
 };
 
 static_assert(sizeof(BatchJob) == 56, "job layout");
-
-struct BatchTables {
-    const float2 *hi, *lo, *tile;
-    int32_t log2N, log2Lo;
-};
 
 // One task: the tile number and a copy of its job (one 64-byte scalar load).
 struct BatchTask {
@@ -96,9 +89,10 @@ struct BatchArgs {
     float2 *ws;
     const BatchTask *tasks;
     const BatchJob *jobs;
-    const BatchTables *tabs;
+    const TopRoots *tabs;
+    const int64_t *members;  // first items of the small transforms, task by task
     const float2 *stw;
-    int32_t stw_off[kMaxOnChipLog2 + 1];
+    int32_t stw_off[kStageMaxLog2 + 1];
     uint32_t njobs;
     uint32_t nq;           // work queues: one per XCD, or one shared queue
     const uint32_t *qbeg;  // tasks of queue q: [qbeg[q], qbeg[q + 1])
@@ -107,202 +101,87 @@ struct BatchArgs {
     uint32_t spin_limit;   // polls before a completion wait gives up (kSpinLimit)
 };
 
-// Tile variant v of a local length 2^l: 2^(12 - l + v) columns per tile;
-// v = 0 one LDS group, v = 1 two groups (16-byte accesses move both).
-// Every variant runs exactly kBT threads with 16 items each.
-constexpr int var_log2T(int l, int v) { return kMaxOnChipLog2 - l + v; }
+// The thread id goes through an empty asm in every variant of a task: the
+// compiler then hoists no variant's per-thread address arithmetic out of it
+// (kept live across the others, it spilled).
+__device__ __forceinline__ int own(int tid) { return int(opaque(uint32_t(tid))); }
 
-// ---- Phase I / Phase III column tiles --------------------------------------
-template <int L, int V, bool COH>
-__device__ __forceinline__ void p1_tile(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
-{
-    constexpr int LT = var_log2T(L, V), H = V ? 2 : 1, EG = 16;
-    static_assert((1 << (L + LT - (H == 2 ? 1 : 0))) / EG == kBT, "tile geometry");
-    fast_tile<L, 2, 1, H, EG, LT, COH>(A.in + J.base, A.ws + J.base, 1u << J.l2, int64_t(tile) << LT, A.stw + A.stw_off[L],
-                                  smem, tid);
-}
+constexpr int pass_lt(int l) { return kTileLog2 - l; }
+// transforms of 2^l points a small task holds: 16 items per thread (shorter
+// ones: one transform per thread)
+constexpr int small_lt(int l) { return l < 4 ? 9 : 13 - l; }
 
-template <int L, int V, int TB>
-__device__ __forceinline__ void p3_tile(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
+constexpr int batch_lds()
 {
-    constexpr int LT = var_log2T(L, V), H = V ? 2 : 1, EG = 16;
-    static_assert((1 << (L + LT - (H == 2 ? 1 : 0))) / EG == kBT, "tile geometry");
-    if constexpr (L % TB == 0) {
-        fast_tile<L, 1, TB, H, EG, LT>(A.out + J.base, A.out + J.base, 1u << J.l1, int64_t(tile) << LT,
-                                       A.stw + A.stw_off[L], smem, tid);
-    }
+    int m = tile_lds(13, 1, 2);  // kOne
+    for (int l = kBatchMinLog2; l <= 13; ++l) m = m < tile_lds(l, small_lt(l), 1) ? tile_lds(l, small_lt(l), 1) : m;
+    for (int l = kPassMin; l <= kPassMax; ++l) m = m < tile_lds(l, pass_lt(l), 2) ? tile_lds(l, pass_lt(l), 2) : m;
+    return m;
 }
-
-template <int L, bool COH>
-__device__ __forceinline__ void p1_len(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
-{
-    if (J.v1 == 0) p1_tile<L, 0, COH>(A, J, tile, smem, tid);
-    else p1_tile<L, 1, COH>(A, J, tile, smem, tid);
-}
-
-template <int L, int V>
-__device__ __forceinline__ void p3_var(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
-{
-    switch (J.t) {
-    case 1: p3_tile<L, V, 1>(A, J, tile, smem, tid); break;
-    case 2: p3_tile<L, V, 2>(A, J, tile, smem, tid); break;
-    default: p3_tile<L, V, 4>(A, J, tile, smem, tid); break;
-    }
-}
+static_assert(2 * (batch_lds() * 8 + 16) <= 160 * 1024, "two workgroups per CU");
 
 template <int L>
-__device__ __forceinline__ void p3_len(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
+__device__ __forceinline__ void run_small_len(const BatchArgs &A, const BatchJob &J, float2 *smem, int tid)
 {
-    if (J.v3 == 0) p3_var<L, 0>(A, J, tile, smem, tid);
-    else p3_var<L, 1>(A, J, tile, smem, tid);
-}
-
-template <bool COH>
-__device__ __forceinline__ void run_p1(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
-{
-    switch (J.l1) {
-    case 6: p1_len<6, COH>(A, J, tile, smem, tid); break;
-    case 7: p1_len<7, COH>(A, J, tile, smem, tid); break;
-    case 8: p1_len<8, COH>(A, J, tile, smem, tid); break;
-    case 9: p1_len<9, COH>(A, J, tile, smem, tid); break;
-    default: p1_len<10, COH>(A, J, tile, smem, tid); break;
-    }
-}
-
-__device__ __forceinline__ void run_p3(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
-{
-    switch (J.l2) {
-    case 6: p3_len<6>(A, J, tile, smem, tid); break;
-    case 7: p3_len<7>(A, J, tile, smem, tid); break;
-    case 8: p3_len<8>(A, J, tile, smem, tid); break;
-    case 9: p3_len<9>(A, J, tile, smem, tid); break;
-    default: p3_len<10>(A, J, tile, smem, tid); break;
-    }
-}
-
-__device__ __forceinline__ MiddlePass middle_of(const BatchArgs &A, const BatchJob &J)
-{
-    const BatchTables T = A.tabs[J.tab];
-    MiddlePass M;
-    M.ws = A.ws + J.base;
-    M.out = A.out + J.base;
-    M.N1 = int64_t(1) << J.l1;
-    M.N2 = int64_t(1) << J.l2;
-    M.t = J.t;
-    M.m1 = J.l1 / J.t;
-    M.m2 = J.l2 / J.t;
-    M.s1 = 0;  // the batched plans use bases that divide both exponents
-    M.s2 = 0;
-    M.tw_hi = T.hi;
-    M.tw_lo = T.lo;
-    M.tw_tile = T.tile;
-    M.log2N = T.log2N;
-    M.log2Lo = T.log2Lo;
-    M.twiddle = 1;
-    M.packed = 1;
-    return M;
-}
-
-// Phase II of the fused pipeline: the same tile bodies as the single-transform
-// kernels (64 rows x 128 columns when N1 >= 128, else 64 x 64).
-template <bool COH>
-__device__ __forceinline__ void run_p2(const BatchArgs &A, const BatchJob &J, uint32_t tile, int tid)
-{
-    const MiddlePass M = middle_of(A, J);
-    if (J.l1 >= 7) middle_packed2_tile<false, true, COH>(M, tile, tid);
-    else middle_packed_tile<false, true, COH>(M, tile, tid);
-}
-
-// ---- whole small transform in one workgroup --------------------------------
-// One local phase over all columns at once: n = 2^LOG2N rows, 2^log2T
-// columns, row length ld.  MODE 2: natural input rows, packed transposed
-// output (Phase I); MODE 1: input row of logical j is pi(j) in base 2^in_t
-// over in_ell digits, natural output rows (Phase III).
-template <int LOG2N, int MODE>
-__device__ __forceinline__ void small_local(const float2 *src, float2 *dst, uint32_t ld, int log2T, int in_t,
-                                            int in_ell, const float2 *stw, float2 *smem, int tid)
-{
-    constexpr int EG = LOG2N < 4 ? (1 << LOG2N) : 16;
-    constexpr int LR0 = stage_log2radix(LOG2N, 0);
-    constexpr int R0 = 1 << LR0;
-    constexpr int NB0 = EG / R0;
-    constexpr int LNR0 = LOG2N - LR0;
-    constexpr int TWN = stage_tw_total(LOG2N);
-    float2 *twl = smem;
-    float2 *lds = smem + ((TWN + 63) & ~63);
-    const int nt = (1 << (LOG2N + log2T)) / EG;  // threads that own butterflies (<= kBT)
-    const bool act = tid < nt;
-    const int Tm = (1 << log2T) - 1;
-    const char *s = reinterpret_cast<const char *>(src);
-    const uint32_t ld8 = ld * 8u;
-    float2 v[EG];
-#pragma unroll
-    for (int e = 0; e < EG; ++e) v[e] = make_float2(0.f, 0.f);
-    if (act) {
-#pragma unroll
-        for (int q = 0; q < NB0; ++q) {
-            const int g = tid + q * nt;
-            const int t = g & Tm, j = g >> log2T;
-#pragma unroll
-            for (int r = 0; r < R0; ++r) {
-                const uint32_t jj = uint32_t(j + (r << LNR0));
-                const uint32_t row = MODE == 1 ? uint32_t(digrev<false>(jj, in_t, in_ell)) : jj;
-                v[q * R0 + r] = *reinterpret_cast<const float2 *>(s + row * ld8 + uint32_t(t) * 8u);
-            }
-        }
-    }
-    copy_twiddles(twl, stw, TWN, tid, kBT);
-    Ctx c;
-    c.lds = lds;
-    c.twl = twl;
-    c.tid = tid;
-    c.nt = nt;
-    c.log2T = log2T;
-    c.dst = reinterpret_cast<char *>(dst);
-    c.ld8 = ld8;
-    c.orow_out = 0;
-    c.k_out = 1;
-    c.out_t = 0;
-    c.out_ell = 0;
-    c.act = act;
-    run_stage<LOG2N, 0, EG, -1, MODE, 1, false, 1>(v, c);
-}
-
-template <int MODE>
-__device__ __forceinline__ void small_phase(int l, const float2 *src, float2 *dst, uint32_t ld, int log2T, int in_t,
-                                            int in_ell, const BatchArgs &A, float2 *smem, int tid)
-{
-    switch (l) {
-    case 1: small_local<1, MODE>(src, dst, ld, log2T, in_t, in_ell, A.stw + A.stw_off[1], smem, tid); break;
-    case 2: small_local<2, MODE>(src, dst, ld, log2T, in_t, in_ell, A.stw + A.stw_off[2], smem, tid); break;
-    case 3: small_local<3, MODE>(src, dst, ld, log2T, in_t, in_ell, A.stw + A.stw_off[3], smem, tid); break;
-    case 4: small_local<4, MODE>(src, dst, ld, log2T, in_t, in_ell, A.stw + A.stw_off[4], smem, tid); break;
-    case 5: small_local<5, MODE>(src, dst, ld, log2T, in_t, in_ell, A.stw + A.stw_off[5], smem, tid); break;
-    default: small_local<6, MODE>(src, dst, ld, log2T, in_t, in_ell, A.stw + A.stw_off[6], smem, tid); break;
-    }
+    static_assert(tile_threads(L, small_lt(L), 1) == kBT, "tile geometry");
+    const int64_t *m = A.members + J.base;
+    const int n = J.count;
+    chip_tile<L, small_lt(L)>(A.in, A.out, [&](int t) { return t < n ? m[t] : int64_t(-1); }, A.stw + A.stw_off[L], smem,
+                              own(tid), false, 0.f);
 }
 
 __device__ __forceinline__ void run_small(const BatchArgs &A, const BatchJob &J, float2 *smem, int tid)
 {
-    const float2 *x = A.in + J.base;
-    float2 *w = A.ws + J.base;
-    float2 *y = A.out + J.base;
-    const int l1 = J.l1, l2 = J.l2, lN = l1 + l2;
-    // Phase I: N1-point DFTs of the N2 columns, packed slab written transposed
-    small_phase<2>(l1, x, w, 1u << l2, l2, 0, 0, A, smem, tid);
-    __syncthreads();
-    // Phase II: row c -> pi_{m2}(c), item v scaled by w_N^{-v c}
-    const BatchTables T = A.tabs[J.tab];
-    const uint32_t N = 1u << lN, n1m = (1u << l1) - 1, lom = (1u << T.log2Lo) - 1;
-    for (uint32_t e = tid; e < N; e += kBT) {
-        const uint32_t c = e >> l1, v = e & n1m;
-        const uint32_t u = uint32_t(digrev<false>(c, J.t, l2 / J.t));
-        const uint32_t r = (v * c) & (N - 1);
-        y[(u << l1) + v] = cmul(w[e], cmul(T.hi[r >> T.log2Lo], T.lo[r & lom]));
+    switch (J.l1) {
+    case 2: run_small_len<2>(A, J, smem, tid); break;
+    case 3: run_small_len<3>(A, J, smem, tid); break;
+    case 4: run_small_len<4>(A, J, smem, tid); break;
+    case 5: run_small_len<5>(A, J, smem, tid); break;
+    case 6: run_small_len<6>(A, J, smem, tid); break;
+    case 7: run_small_len<7>(A, J, smem, tid); break;
+    case 8: run_small_len<8>(A, J, smem, tid); break;
+    case 9: run_small_len<9>(A, J, smem, tid); break;
+    case 10: run_small_len<10>(A, J, smem, tid); break;
+    case 11: run_small_len<11>(A, J, smem, tid); break;
+    case 12: run_small_len<12>(A, J, smem, tid); break;
+    default: run_small_len<13>(A, J, smem, tid); break;
     }
-    __syncthreads();
-    // Phase III: N2-point DFTs of the N1 columns, input rows pi_{m2}, in place
-    small_phase<1>(l2, y, y, 1u << l1, l1, J.t, l2 / J.t, A, smem, tid);
+}
+
+template <int L, bool COH>
+__device__ __forceinline__ void run_a_len(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
+{
+    static_assert(tile_threads(L, pass_lt(L), 2) == kBT, "tile geometry");
+    pass_a_tile<L, pass_lt(L), 2, COH>(A.in + J.base, A.ws + J.base, J.l2, pass_lt(J.l2), tile << pass_lt(L),
+                                       A.stw + A.stw_off[L], smem, own(tid), false);
+}
+
+template <int L>
+__device__ __forceinline__ void run_b_len(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
+{
+    pass_b_tile<L, pass_lt(L), 2>(A.ws + J.base, A.out + J.base, J.l1, tile << pass_lt(L), A.tabs[J.tab],
+                                  A.stw + A.stw_off[L], smem, own(tid), 0.f);
+}
+
+template <bool COH>
+__device__ __forceinline__ void run_a(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
+{
+    switch (J.l1) {
+    case 7: run_a_len<7, COH>(A, J, tile, smem, tid); break;
+    case 8: run_a_len<8, COH>(A, J, tile, smem, tid); break;
+    case 9: run_a_len<9, COH>(A, J, tile, smem, tid); break;
+    default: run_a_len<10, COH>(A, J, tile, smem, tid); break;
+    }
+}
+
+__device__ __forceinline__ void run_b(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
+{
+    switch (J.l2) {
+    case 7: run_b_len<7>(A, J, tile, smem, tid); break;
+    case 8: run_b_len<8>(A, J, tile, smem, tid); break;
+    case 9: run_b_len<9>(A, J, tile, smem, tid); break;
+    default: run_b_len<10>(A, J, tile, smem, tid); break;
+    }
 }
 
 // Polls with relaxed loads (an acquire load also drops this XCD's cached
@@ -329,9 +208,9 @@ __device__ __forceinline__ void wait_for(const BatchArgs &A, int32_t dep, uint32
 // COH = true: one queue shared by all XCDs; the tiles other tasks read are
 // written with device-coherent stores instead.
 template <bool COH>
-__global__ __launch_bounds__(kBT) void batch_kernel(BatchArgs A)
+__global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void batch_kernel(BatchArgs A)
 {
-    extern __shared__ float2 smem[];
+    __shared__ float2 smem[batch_lds()];
     __shared__ uint32_t s_ticket;
     __shared__ int s_last;
     const int tid = threadIdx.x;
@@ -353,17 +232,15 @@ __global__ __launch_bounds__(kBT) void batch_kernel(BatchArgs A)
             if (tid == 0) wait_for(A, J.dep, uint32_t(J.dep_tiles));
             __syncthreads();
         }
-        // The thread id goes through an empty asm in every iteration: the
-        // compiler then cannot hoist the per-thread address arithmetic of all
-        // task variants out of the loop, which would keep every variant's
-        // values live at once.
-        int ltid = tid;
-        __asm__ volatile("" : "+v"(ltid));
         switch (J.kind) {
-        case kP1: run_p1<COH>(A, J, task.tile, smem, ltid); break;
-        case kP2: run_p2<COH>(A, J, task.tile, ltid); break;
-        case kP3: run_p3(A, J, task.tile, smem, ltid); break;
-        default: run_small(A, J, smem, ltid); break;
+        case kPassA: run_a<COH>(A, J, task.tile, smem, tid); break;
+        case kPassB: run_b(A, J, task.tile, smem, tid); break;
+        case kOne: {
+            const TopRoots T = A.tabs[J.tab];
+            chip14_tile(A.in + J.base, A.out + J.base, A.stw + A.stw_off[13], T.hi, T.lo, smem, own(tid), false, 0.f);
+            break;
+        }
+        default: run_small(A, J, smem, tid); break;
         }
         // Completion: once every wave has seen its stores complete (vmcnt 0)
         // a relaxed device-scope increment publishes the tile (the ordering a
@@ -411,70 +288,20 @@ int ilog2_pow2(int64_t n)
     return l;
 }
 
-bool is_small(int k) { return k <= kSmallMaxLog2; }
-
-// Valid per-size plans, default first.
+// Valid per-size plans, default first: balanced split, b = 2.  The plan of
+// transforms of at most 2^14 items has no choice that matters (one workgroup
+// runs all of it); of larger ones the split decides the lengths of the two
+// passes.  b is reported and has no effect on the result or the time.
 std::vector<SizePlan> candidates(int k)
 {
     std::vector<SizePlan> out;
-    auto variants = [](int l, int lcols) {
-        std::vector<int> v;
-        for (int x = 0; x <= 1; ++x)
-            if (var_log2T(l, x) <= lcols) v.push_back(x);
-        return v;
-    };
-    std::vector<int> splits;
-    if (is_small(k)) {
-        splits = {(k + 1) / 2, k / 2};
-        if (splits[0] == splits[1]) splits.pop_back();
-    } else {
-        const int lo = std::max(kBigMinLocal, k - kBigMaxLocal), hi = std::min(kBigMaxLocal, k - kBigMinLocal);
-        int mid = (k + 1) / 2;
-        mid = std::min(std::max(mid, lo), hi);
-        splits.push_back(mid);
+    const int mid = (k + 1) / 2;
+    const int lo = std::max(kPassMin, k - kPassMax), hi = std::min(kPassMax, k - kPassMin);
+    out.push_back({mid, k - mid, 1, 0, 0});
+    if (k > kChipMaxLog2)
         for (int l = lo; l <= hi; ++l)
-            if (l != mid) splits.push_back(l);
-    }
-    for (int l1 : splits) {
-        const int l2 = k - l1;
-        for (int t : {1, 2, 4}) {
-            if (l1 % t || l2 % t) continue;
-            if (is_small(k)) {
-                SizePlan sp;
-                sp.l1 = l1;
-                sp.l2 = l2;
-                sp.t = t;
-                out.push_back(sp);
-                continue;
-            }
-            for (int v1 : variants(l1, l2))
-                for (int v3 : variants(l2, l1)) {
-                    SizePlan sp;
-                    sp.l1 = l1;
-                    sp.l2 = l2;
-                    sp.t = t;
-                    sp.v1 = v1;
-                    sp.v3 = v3;
-                    out.push_back(sp);
-                }
-        }
-    }
-    // default first: balanced split, b = 2, two LDS groups for the long lengths
-    const int pref = splits.front();
-    auto score = [&](const SizePlan &s) {
-        const int dv = is_small(k) ? 0 : int(s.v1 != (s.l1 >= 9 ? 1 : 0)) + int(s.v3 != (s.l2 >= 9 ? 1 : 0));
-        return (s.l1 != pref) * 8 + (s.t != 1) * 4 + dv;
-    };
-    std::stable_sort(out.begin(), out.end(), [&](const SizePlan &a, const SizePlan &b) { return score(a) < score(b); });
+            if (l != mid) out.push_back({l, k - l, 1, 0, 0});
     return out;
-}
-
-size_t lds_bytes_for(int maxl)
-{
-    int64_t twn = 0;
-    for (int l = 1; l <= maxl; ++l) twn = std::max<int64_t>(twn, stage_tw_total(l));
-    const int64_t items = int64_t(1) << kMaxOnChipLog2;  // one LDS group holds 4096 items
-    return size_t(((twn + 63) & ~int64_t(63)) + items + ((items >> 6) << 2) + 4) * sizeof(float2);
 }
 
 }  // namespace
@@ -482,7 +309,6 @@ size_t lds_bytes_for(int maxl)
 
 using paco::BatchArgs;
 using paco::BatchJob;
-using paco::BatchTables;
 using paco::BatchTask;
 using paco::SizePlan;
 
@@ -495,7 +321,6 @@ struct paco_batch_plan_s {
     void *dev = nullptr;
     BatchArgs args{};
     int grid = 0;
-    size_t lds = 0;
     int64_t gap = 0;
     int nq = 1;        // work queues
     bool coh = false;  // one queue served by several XCDs: coherent stores
@@ -523,13 +348,13 @@ const void *kernel_of(bool coh)
                : reinterpret_cast<const void *>(paco::batch_kernel<false>);
 }
 
-int resident_workgroups(bool coh, size_t lds)
+int resident_workgroups(bool coh)
 {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    const hipError_t e = coh ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, paco::batch_kernel<true>, paco::kBT, lds)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, paco::batch_kernel<false>, paco::kBT, lds);
+    const hipError_t e = coh ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, paco::batch_kernel<true>, paco::kBT, 0)
+                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, paco::batch_kernel<false>, paco::kBT, 0);
     if (e != hipSuccess) return 0;
     return cus * std::max(per, 1);
 }
@@ -555,17 +380,23 @@ paco_status build_batch(paco_batch_plan_s *P)
     std::vector<int> ks;
     for (auto &kv : P->plans) ks.push_back(kv.first);
     std::map<int, int> tab_of;
-    std::vector<std::vector<float2>> his, los, tiles;
+    std::vector<std::vector<float2>> his, los, cws;
     for (int k : ks) {
+        if (k < kChipMaxLog2) continue;  // no table but the stages'
         tab_of[k] = int(his.size());
-        std::vector<float2> hi, lo, tile;
-        middle_tables(k, hi, lo, tile);
+        std::vector<float2> hi, lo, cw;
+        top_tables(k, hi, lo);
+        if (k > kChipMaxLog2) {
+            const int64_t n = int64_t(16) << P->plans[k].l1;
+            cw.resize(size_t(n));
+            for (int64_t i = 0; i < n; ++i) cw[i] = root_neg(i, n);
+        }
         his.push_back(std::move(hi));
         los.push_back(std::move(lo));
-        tiles.push_back(std::move(tile));
+        cws.push_back(std::move(cw));
     }
     std::vector<float2> stw;
-    int64_t stw_off[kMaxOnChipLog2 + 1];
+    int64_t stw_off[kStageMaxLog2 + 1];
     if (!stage_tables(stw, stw_off)) return bfail(PACO_ERR_INVALID_ARG, "internal: stage twiddle layout mismatch");
 
     // ---- queues: transforms to XCDs, largest first onto the least loaded ------
@@ -574,72 +405,94 @@ paco_status build_batch(paco_batch_plan_s *P)
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&nxcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess)
         nxcd = 0;  // unknown: one shared, coherent queue
-    P->coh = nx == 1 && nxcd != 1;  // several XCDs serve one queue
-    P->nq = nx;
     std::vector<int32_t> order(count);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return P->N[a] > P->N[b]; });
-    std::vector<int64_t> load(nx, 0);
-    std::vector<std::vector<int32_t>> qorder(nx);
-    for (int32_t i : order) {
-        const int qi = int(std::min_element(load.begin(), load.end()) - load.begin());
-        load[qi] += P->N[i];
-        qorder[qi].push_back(i);
+    std::vector<std::vector<int32_t>> qorder;
+    const auto deal = [&](int n) {  // returns the largest queue's items
+        std::vector<int64_t> load(n, 0);
+        qorder.assign(n, {});
+        for (int32_t i : order) {
+            const int qi = int(std::min_element(load.begin(), load.end()) - load.begin());
+            load[qi] += P->N[i];
+            qorder[qi].push_back(i);
+        }
+        return *std::max_element(load.begin(), load.end());
+    };
+    // A queue per XCD keeps a transform's intermediate in that XCD's L2, but
+    // a transform then runs on one XCD alone: where the fullest queue would
+    // hold more than 1.5 times its share (a few large transforms), all XCDs
+    // serve one queue
+    if (deal(nx) * nx > P->total + P->total / 2 && nx > 1) {
+        nx = 1;
+        deal(nx);
     }
+    P->coh = nx == 1 && nxcd != 1;  // several XCDs serve one queue
+    P->nq = nx;
+    const int resident = resident_workgroups(P->coh);
+    if (resident <= 0) return bfail(PACO_ERR_HIP, "occupancy query failed");
 
     // ---- jobs ---------------------------------------------------------------
     std::vector<BatchJob> jobs;
-    struct Chain { int32_t first; };  // P1 job of a large transform (P2 = +1, P3 = +2)
+    std::vector<int64_t> members;
+    struct Chain { int32_t first; };  // pass-A job of a large transform (pass B = +1)
     std::vector<std::vector<Chain>> chains(nx);
     std::vector<std::vector<int32_t>> smalls(nx);
-    int maxl = 1;
-    for (int qi = 0; qi < nx; ++qi)
-    for (int32_t i : qorder[qi]) {
-        const int k = ilog2_pow2(P->N[i]);
-        const SizePlan &sp = P->plans[k];
-        BatchJob J{};
-        J.base = P->offset[i];
-        J.l1 = sp.l1;
-        J.l2 = sp.l2;
-        J.t = sp.t;
-        J.v1 = sp.v1;
-        J.v3 = sp.v3;
-        J.tab = tab_of[k];
-        J.dep = -1;
-        maxl = std::max(maxl, std::max(sp.l1, sp.l2));
-        if (is_small(k)) {
-            J.kind = kSmall;
+    for (int qi = 0; qi < nx; ++qi) {
+        // items of a small task: a full tile, less where that would leave
+        // workgroups of the queue without one
+        int64_t small_items = 0;
+        for (int32_t i : qorder[qi])
+            if (ilog2_pow2(P->N[i]) < kChipMaxLog2) small_items += P->N[i];
+        const int64_t share = small_items * nx / resident + 1;
+        for (size_t o = 0; o < qorder[qi].size(); ++o) {
+            const int32_t i = qorder[qi][o];
+            const int k = ilog2_pow2(P->N[i]);
+            const SizePlan &sp = P->plans[k];
+            BatchJob J{};
+            J.base = P->offset[i];
+            J.l1 = sp.l1;
+            J.l2 = sp.l2;
+            J.dep = -1;
             J.ntiles = 1;
-            smalls[qi].push_back(int32_t(jobs.size()));
-            jobs.push_back(J);
-            continue;
+            if (k < kChipMaxLog2) {  // with the next transforms of its size
+                const int64_t most = std::max<int64_t>(1, std::min<int64_t>(share >> k, int64_t(1) << small_lt(k)));
+                J.kind = kSmall;
+                J.l1 = k;
+                J.base = int64_t(members.size());
+                while (o < qorder[qi].size() && P->N[qorder[qi][o]] == P->N[i] && J.count < most) {
+                    members.push_back(P->offset[qorder[qi][o]]);
+                    ++J.count;
+                    ++o;
+                }
+                --o;
+                smalls[qi].push_back(int32_t(jobs.size()));
+                jobs.push_back(J);
+                continue;
+            }
+            J.tab = tab_of[k];
+            if (k == kChipMaxLog2) {
+                J.kind = kOne;
+                smalls[qi].push_back(int32_t(jobs.size()));
+                jobs.push_back(J);
+                continue;
+            }
+            const int32_t first = int32_t(jobs.size());
+            BatchJob a = J, c = J;
+            a.kind = kPassA;
+            a.ntiles = 1 << (sp.l2 - pass_lt(sp.l1));
+            a.signal = 1;
+            c.kind = kPassB;
+            c.ntiles = 1 << (sp.l1 - pass_lt(sp.l2));
+            c.dep = first;
+            c.dep_tiles = a.ntiles;
+            jobs.push_back(a);
+            jobs.push_back(c);
+            chains[qi].push_back({first});
         }
-        const int32_t first = int32_t(jobs.size());
-        BatchJob a = J, m = J, c = J;
-        a.kind = kP1;
-        a.ntiles = int32_t((int64_t(1) << sp.l2) >> var_log2T(sp.l1, sp.v1));
-        a.signal = 1;
-        m.kind = kP2;
-        m.ntiles = int32_t(((int64_t(1) << sp.l1) >> (sp.l1 >= 7 ? 7 : 6)) * ((int64_t(1) << sp.l2) >> 6));
-        m.dep = first;
-        m.dep_tiles = a.ntiles;
-        m.signal = 1;
-        c.kind = kP3;
-        c.ntiles = int32_t((int64_t(1) << sp.l1) >> var_log2T(sp.l2, sp.v3));
-        c.dep = first + 1;
-        c.dep_tiles = m.ntiles;
-        jobs.push_back(a);
-        jobs.push_back(m);
-        jobs.push_back(c);
-        chains[qi].push_back({first});
     }
 
     // ---- launch geometry -----------------------------------------------------
-    P->lds = lds_bytes_for(std::min(maxl, kMaxOnChipLog2));
-    hipError_t e = hipFuncSetAttribute(kernel_of(P->coh), hipFuncAttributeMaxDynamicSharedMemorySize, int(P->lds));
-    if (e != hipSuccess) return bhip(e, "hipFuncSetAttribute");
-    const int resident = resident_workgroups(P->coh, P->lds);
-    if (resident <= 0) return bfail(PACO_ERR_HIP, "occupancy query failed");
     // per queue: a job's successor is emitted about `gap` tiles after it, a
     // few times the workgroups that serve the queue
     P->gap = 4 * int64_t(resident) / nx;
@@ -654,7 +507,7 @@ paco_status build_batch(paco_batch_plan_s *P)
         std::deque<std::pair<int64_t, int32_t>> pending;  // (ready position, job)
         auto emit = [&](int32_t j) {
             for (int32_t t = 0; t < jobs[j].ntiles; ++t) tasks.push_back({jobs[j], uint32_t(j), uint32_t(t)});
-            if (jobs[j].kind == kP1 || jobs[j].kind == kP2)
+            if (jobs[j].kind == kPassA)
                 pending.push_back({int64_t(tasks.size()) - base + P->gap, j + 1});
         };
         auto pos = [&]() { return int64_t(tasks.size()) - base; };
@@ -690,14 +543,15 @@ paco_status build_batch(paco_batch_plan_s *P)
         return pieces.size() - 1;
     };
     const size_t i_stw = add(stw.data(), stw.size() * 8);
-    std::vector<size_t> i_hi, i_lo, i_tile;
+    std::vector<size_t> i_hi, i_lo, i_cw;
     for (size_t s = 0; s < his.size(); ++s) {
         i_hi.push_back(add(his[s].data(), his[s].size() * 8));
         i_lo.push_back(add(los[s].data(), los[s].size() * 8));
-        i_tile.push_back(add(tiles[s].data(), tiles[s].size() * 8));
+        i_cw.push_back(add(cws[s].data(), cws[s].size() * 8));
     }
-    std::vector<BatchTables> tabs(his.size());
-    const size_t i_tabs = add(nullptr, tabs.size() * sizeof(BatchTables));
+    std::vector<TopRoots> tabs(his.size());
+    const size_t i_tabs = add(nullptr, tabs.size() * sizeof(TopRoots));
+    const size_t i_mem = add(members.data(), members.size() * 8);
     const size_t i_jobs = add(jobs.data(), jobs.size() * sizeof(BatchJob));
     const size_t i_tasks = add(tasks.data(), tasks.size() * sizeof(BatchTask));
     const size_t i_qbeg = add(qbeg.data(), qbeg.size() * 4);
@@ -709,7 +563,7 @@ paco_status build_batch(paco_batch_plan_s *P)
         pc.off = total;
         total += (pc.bytes + 255) & ~size_t(255);
     }
-    e = hipMalloc(&P->dev, total);
+    hipError_t e = hipMalloc(&P->dev, total);
     if (e != hipSuccess) {
         P->dev = nullptr;
         return bfail(PACO_ERR_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -718,9 +572,11 @@ paco_status build_batch(paco_batch_plan_s *P)
     for (size_t s = 0; s < his.size(); ++s) {
         tabs[s].hi = reinterpret_cast<const float2 *>(at(i_hi[s]));
         tabs[s].lo = reinterpret_cast<const float2 *>(at(i_lo[s]));
-        tabs[s].tile = reinterpret_cast<const float2 *>(at(i_tile[s]));
-        tabs[s].log2N = ks[s];
-        tabs[s].log2Lo = middle_log2lo(ks[s]);
+        tabs[s].cw = reinterpret_cast<const float2 *>(at(i_cw[s]));
+    }
+    for (const auto &kt : tab_of) {
+        tabs[kt.second].log2N = kt.first;
+        tabs[kt.second].log2Lo = middle_log2lo(kt.first);
     }
     pieces[i_tabs].src = tabs.data();
     std::vector<unsigned char> staging(total, 0);  // counters start at zero
@@ -732,9 +588,10 @@ paco_status build_batch(paco_batch_plan_s *P)
     BatchArgs &A = P->args;
     A.tasks = reinterpret_cast<const BatchTask *>(at(i_tasks));
     A.jobs = reinterpret_cast<const BatchJob *>(at(i_jobs));
-    A.tabs = reinterpret_cast<const BatchTables *>(at(i_tabs));
+    A.tabs = reinterpret_cast<const TopRoots *>(at(i_tabs));
+    A.members = reinterpret_cast<const int64_t *>(at(i_mem));
     A.stw = reinterpret_cast<const float2 *>(at(i_stw));
-    for (int l = 0; l <= kMaxOnChipLog2; ++l) A.stw_off[l] = int32_t(stw_off[l]);
+    for (int l = 0; l <= kStageMaxLog2; ++l) A.stw_off[l] = int32_t(stw_off[l]);
     A.njobs = uint32_t(jobs.size());
     A.nq = uint32_t(nx);
     A.qbeg = reinterpret_cast<const uint32_t *>(at(i_qbeg));
@@ -754,13 +611,13 @@ paco_status build_batch(paco_batch_plan_s *P)
     std::snprintf(buf, sizeof buf,
                   "batch[%d transforms, %lld items, %zu jobs, %zu tasks, %d %s, grid %d x %d, lds %zu, gap %lld]",
                   count, (long long)P->total, jobs.size(), tasks.size(), nx,
-                  P->coh ? "shared queue (coherent stores)" : "queues (one per XCD)", P->grid, kBT, P->lds,
+                  P->coh ? "shared queue (coherent stores)" : "queues (one per XCD)", P->grid, kBT, size_t(paco::batch_lds()) * 8,
                   (long long)P->gap);
     P->desc = buf;
     for (auto &kv : P->plans) {
         const SizePlan &sp = kv.second;
-        std::snprintf(buf, sizeof buf, " 2^%d:%dx%d,b=%d,T1=%d,T3=%d%s", kv.first, 1 << sp.l1, 1 << sp.l2, 1 << sp.t,
-                      1 << var_log2T(sp.l1, sp.v1), 1 << var_log2T(sp.l2, sp.v3), is_small(kv.first) ? "(wg)" : "");
+        std::snprintf(buf, sizeof buf, " 2^%d:%dx%d,b=%d%s", kv.first, 1 << sp.l1, 1 << sp.l2, 1 << sp.t,
+                      kv.first <= kChipMaxLog2 ? "(wg)" : "");
         P->desc += buf;
     }
     if (const char *lg = std::getenv("PACO_LOG"))  // plan summary on stderr
@@ -775,7 +632,7 @@ hipError_t launch_batch(const paco_batch_plan_s *P, const void *in, void *out, v
     A.out = static_cast<float2 *>(out);
     A.ws = static_cast<float2 *>(ws);
     void *args[] = {&A};
-    return hipLaunchKernel(kernel_of(P->coh), dim3(unsigned(P->grid)), dim3(paco::kBT), args, P->lds, s);
+    return hipLaunchKernel(kernel_of(P->coh), dim3(unsigned(P->grid)), dim3(paco::kBT), args, 0, s);
 }
 
 void free_plan(paco_batch_plan_s *P)
@@ -807,7 +664,10 @@ paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
         const int k = ks[ki];
         const int64_t copies = std::min<int64_t>(std::max<int64_t>(1, items >> k), 16384);
         float best = 1e30f;
-        for (const SizePlan &sp : paco::candidates(k)) {
+        const std::vector<SizePlan> cand = paco::candidates(k);
+        plans[k] = cand.front();
+        if (cand.size() == 1) continue;
+        for (const SizePlan &sp : cand) {
             paco_batch_plan_s *T = new (std::nothrow) paco_batch_plan_s();
             if (!T) { st = bfail(PACO_ERR_ALLOC, "host allocation failed"); break; }
             T->count = int32_t(copies);
@@ -844,10 +704,16 @@ paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
     return st;
 }
 
+// A cached plan is used if its split is one of the candidates' (any split of
+// a transform of one workgroup) and its b is a base of both sides; the last
+// two fields are tile variants of an earlier kernel and have no effect.
 bool valid_plan(int k, const SizePlan &sp)
 {
+    if (sp.t != 1 && sp.t != 2 && sp.t != 4) return false;
+    if (sp.l1 < 1 || sp.l2 < 1 || sp.l1 + sp.l2 != k || sp.l1 % sp.t || sp.l2 % sp.t) return false;
+    if (k <= paco::kChipMaxLog2) return true;
     for (const SizePlan &c : paco::candidates(k))
-        if (c.l1 == sp.l1 && c.l2 == sp.l2 && c.t == sp.t && c.v1 == sp.v1 && c.v3 == sp.v3) return true;
+        if (c.l1 == sp.l1) return true;
     return false;
 }
 
@@ -950,11 +816,6 @@ paco_status paco_batch_plan_create_ex(paco_batch_plan **bp, int32_t count, const
     if (e != hipSuccess) {
         free_plan(P);
         return bhip(e, "hipGetDevice");
-    }
-    e = paco::local_fft_prepare();
-    if (e != hipSuccess) {
-        free_plan(P);
-        return bhip(e, "hipFuncSetAttribute");
     }
     // per-size plans: cache file, then tuning (unless PACO_BATCH_NO_TUNE), else defaults
     std::map<int, SizePlan> plans;

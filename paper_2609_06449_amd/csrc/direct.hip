@@ -1,0 +1,146 @@
+// The direct form of a single FP32 transform of at most 2^22 items: one
+// workgroup up to 2^14 items, two column passes above (tile.h).
+//
+// At these sizes a call is launches and latency, not bytes: the phases' three
+// dependent launches took 14.3 us at 2^12, 16.7 at 2^16, 24.2 at 2^20 and 52.9
+// at 2^22 (calls back to back), where a copy of the data takes 0.01, 0.2, 3
+// and 12 us.  Lemma 1 holds for any digit-aligned split of N, so the form
+// takes the one with the fewest launches: 7.6, 9.6, 14.7 and 32.4 us.  One
+// workgroup's kernel takes 4.7 us at 2^12, 6.7 at 2^13 and 12.2 at 2^14,
+// where two passes of 3.8 and 4.3 us would be as fast back to back but pay
+// the second launch when a call is waited for.
+#include "tile.h"
+
+namespace paco {
+namespace {
+
+struct DirectArgs {
+    const float2 *src;
+    float2 *dst;
+    const float2 *stw;
+    TopRoots top;
+    int32_t l1, l2;
+    int32_t conj_in;
+    float out_scale;
+};
+
+template <int L>
+__global__ __launch_bounds__(tile_threads(L, 0, 1)) void direct_chip_kernel(DirectArgs P)
+{
+    __shared__ float2 smem[tile_lds(L, 0, 1)];
+    chip_tile<L, 0>(P.src, P.dst, [](int) { return int64_t(0); }, P.stw, smem, threadIdx.x, P.conj_in != 0, P.out_scale);
+}
+
+__global__ __launch_bounds__(512) void direct_chip14_kernel(DirectArgs P)
+{
+    __shared__ float2 smem[tile_lds(13, 1, 2)];
+    chip14_tile(P.src, P.dst, P.stw, P.top.hi, P.top.lo, smem, threadIdx.x, P.conj_in != 0, P.out_scale);
+}
+
+// Tiles of 4 columns: 32-byte runs of x and of y, which the tiles beside it on
+// the same XCD (tile_order) complete to lines in its L2.  What bounds a pass
+// here is its launch and one chain of load, arithmetic, store per workgroup,
+// so the most workgroups win: 4 columns against 8 in both passes took 11.2
+// against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
+// 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
+constexpr int kLT = 2;
+
+template <int L>
+__global__ __launch_bounds__(tile_threads(L, kLT, 1)) void direct_a_kernel(DirectArgs P)
+{
+    __shared__ float2 smem[tile_lds(L, kLT, 1)];
+    pass_a_tile<L, kLT, 1, false>(P.src, P.dst, P.l2, kLT, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.stw,
+                                  smem, threadIdx.x, P.conj_in != 0);
+}
+
+template <int L>
+__global__ __launch_bounds__(tile_threads(L, kLT, 1)) void direct_b_kernel(DirectArgs P)
+{
+    __shared__ float2 smem[tile_lds(L, kLT, 1)];
+    pass_b_tile<L, kLT, 1>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.top, P.stw, smem,
+                           threadIdx.x, P.out_scale);
+}
+
+template <int L>
+void launch_pass(bool b, unsigned tiles, const DirectArgs &a, hipStream_t s)
+{
+    if (b) hipLaunchKernelGGL(direct_b_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, 1)), 0, s, a);
+    else hipLaunchKernelGGL(direct_a_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, 1)), 0, s, a);
+}
+
+// one pass of 2^l points over 2^lcols columns
+hipError_t pass(bool b, int l, int lcols, const DirectArgs &a, hipStream_t s)
+{
+    const unsigned tiles = 1u << (lcols - kLT);
+    switch (l) {
+    case 7: launch_pass<7>(b, tiles, a, s); break;
+    case 8: launch_pass<8>(b, tiles, a, s); break;
+    case 9: launch_pass<9>(b, tiles, a, s); break;
+    case 10: launch_pass<10>(b, tiles, a, s); break;
+    case 11: launch_pass<11>(b, tiles, a, s); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <int L>
+void chip(const DirectArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(direct_chip_kernel<L>, dim3(1), dim3(tile_threads(L, 0, 1)), 0, s, a);
+}
+
+}  // namespace
+
+DirectForm direct_form(int log2N)
+{
+    DirectForm f{};
+    f.log2N = log2N;
+    if (log2N <= kDirectChipLog2) return f;
+    f.l1 = (log2N + 1) / 2;
+    f.l2 = log2N / 2;
+    return f;
+}
+
+hipError_t launch_direct(const DirectForm &f, const float2 *in, float2 *out, float2 *ws, bool inverse, hipStream_t s)
+{
+    DirectArgs a{};
+    a.top = {f.hi, f.lo, f.cw, f.log2N, f.log2Lo};
+    a.l1 = f.l1;
+    a.l2 = f.l2;
+    const float scale = inverse ? 1.0f / float(int64_t(1) << f.log2N) : 0.f;  // 2^-log2 N: exact
+    a.src = in;
+    a.stw = f.stw1;
+    a.conj_in = inverse ? 1 : 0;
+    if (f.log2N <= kDirectChipLog2) {
+        a.dst = out;
+        a.out_scale = scale;
+        switch (f.log2N) {
+        case 2: chip<2>(a, s); break;
+        case 3: chip<3>(a, s); break;
+        case 4: chip<4>(a, s); break;
+        case 5: chip<5>(a, s); break;
+        case 6: chip<6>(a, s); break;
+        case 7: chip<7>(a, s); break;
+        case 8: chip<8>(a, s); break;
+        case 9: chip<9>(a, s); break;
+        case 10: chip<10>(a, s); break;
+        case 11: chip<11>(a, s); break;
+        case 12: chip<12>(a, s); break;
+        case 13: chip<13>(a, s); break;
+        case 14: hipLaunchKernelGGL(direct_chip14_kernel, dim3(1), dim3(512), 0, s, a); break;
+        default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
+    a.dst = ws;
+    hipError_t e = pass(false, f.l1, f.l2, a, s);
+    if (e != hipSuccess) return e;
+    a.src = ws;
+    a.dst = out;
+    a.stw = f.stw2;
+    a.conj_in = 0;
+    a.out_scale = scale;
+    return pass(true, f.l2, f.l1, a, s);
+}
+
+}  // namespace paco

@@ -80,9 +80,8 @@ __global__ __launch_bounds__(generic_max_threads(PREC)) void local_fft_kernel(Lo
     c.out_t = P.out_t;
     c.out_ell = P.out_ell;
     c.out_s = P.out_s;
-    c.act = true;
     c.oscale = P.out_scale;
-    run_stage<LOG2N, 0, EG, -1, -1, 1, GEN, 1, false, PREC>(v, c);
+    run_stage<LOG2N, 0, EG, -1, -1, 1, GEN, 1, PREC>(v, c);
 }
 
 template <int LOG2N, int MODE, int TB, int H, int EG, int PREC>
@@ -106,7 +105,7 @@ __global__ __launch_bounds__(fast_threads(LOG2N, H, EG)) void local_fft_fast_ker
     // reads that buffer in column tiles and finds it in the MALL
     // (streaming there measured 160 -> 180 us per 2^24 transform, against
     // 194 -> 177 us for the packed three-pass form)
-    fast_tile<LOG2N, MODE, TB, H, EG, LT, false, PREC>(P.src, P.dst, uint32_t(P.ld), col0, P.stw, smem, threadIdx.x,
+    fast_tile<LOG2N, MODE, TB, H, EG, LT, PREC>(P.src, P.dst, uint32_t(P.ld), col0, P.stw, smem, threadIdx.x,
                                                        &top, P.conj_in != 0, P.out_scale, MODE == 2);
 }
 

@@ -1,6 +1,4 @@
-// Phase II tile bodies of the fused pipeline, shared by the single-transform
-// kernels (middle.hip) and the batched persistent kernel (batch.hip).
-// COH: device-coherent result stores (st2/st4 in stages.h).
+// Phase II tile bodies of the fused pipeline (middle.hip).
 #pragma once
 
 #include "stages.h"
@@ -19,7 +17,7 @@ constexpr int kMidPerThread = kMidTile * kMidTile / kMidThreads;  // 16
 // c x 64 columns v; wave w takes rows c0 + w + 4q, lane = column, so every
 // load and store is a 512-byte run and the row index, its digit reversal
 // and the per-row twiddle factor are wave-uniform (scalar) values.
-template <bool GEN, bool TW, bool COH = false>
+template <bool GEN, bool TW>
 __device__ __forceinline__ void middle_packed_tile(const MiddlePass &P, int64_t blk, int tid)
 {
     const int64_t nvt = P.N1 >> 6;
@@ -53,13 +51,13 @@ __device__ __forceinline__ void middle_packed_tile(const MiddlePass &P, int64_t 
             const float2 wc = cmul(P.tw_hi[r >> P.log2Lo], P.tw_lo[r & Lm]);
             y = cmul(y, cmul(wc, cmul(rw, t4[q])));
         }
-        st2<COH>(reinterpret_cast<char *>(P.out + u * P.N1 + v0 + lane), y);
+        P.out[u * P.N1 + v0 + lane] = y;
     }
 }
 
 // The same with two adjacent columns per lane: a workgroup owns 64 rows x
 // 128 columns and every load and store is a 1 KB run of 16-byte accesses.
-template <bool GEN, bool TW, bool COH = false>
+template <bool GEN, bool TW>
 __device__ __forceinline__ void middle_packed2_tile(const MiddlePass &P, int64_t blk, int tid)
 {
     const int64_t nvt = P.N1 >> 7;
@@ -96,7 +94,7 @@ __device__ __forceinline__ void middle_packed2_tile(const MiddlePass &P, int64_t
             y0 = cmul(y0, cmul(wc, cmul(rw0, make_float2(t4[q].x, t4[q].y))));
             y1 = cmul(y1, cmul(wc, cmul(rw1, make_float2(t4[q].z, t4[q].w))));
         }
-        st4<COH>(reinterpret_cast<char *>(P.out + u * P.N1 + v0 + vi), make_float4(y0.x, y0.y, y1.x, y1.y));
+        *reinterpret_cast<float4 *>(P.out + u * P.N1 + v0 + vi) = make_float4(y0.x, y0.y, y1.x, y1.y);
     }
 }
 

@@ -22,6 +22,8 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 
 // Largest transform length one local pass keeps on chip (LDS + registers).
 constexpr int kMaxOnChipLog2 = 12;
+// Largest length the stage tables cover (tiles of the direct form, tile.h).
+constexpr int kStageMaxLog2 = 13;
 
 // ---------------------------------------------------------------------------
 // Stage plan of an on-chip transform of length n = 2^l: radix-16 Stockham
@@ -204,6 +206,20 @@ struct SymPass {
     uint32_t resident2;             // pass 2 of the wide form (N2 = 2^15), likewise
 };
 
+// The direct form (direct.hip), FP32, N <= 2^22: one launch of one workgroup
+// up to 2^14 items, else two column passes over N = 2^l1 2^l2 (tile.h).  The
+// split of N is the library's own: neither N1 x N2 nor b nor p of the plan
+// enters the result.
+constexpr int kDirectChipLog2 = 14;  // the largest transform of one workgroup
+constexpr int kDirectMaxLog2 = 22;
+struct DirectForm {
+    int32_t log2N, l1, l2;           // two passes: pass A 2^l1 points over 2^l2 columns, pass B the reverse
+    const float2 *stw1, *stw2;       // stage tables of the two lengths (one workgroup: stw1)
+    const float2 *hi, *lo;           // two-level table of w_N (split at 2^log2Lo)
+    int32_t log2Lo;
+    const float2 *cw;                // w_{16 M1}^{-k}, k < 16 M1 = 2^(l1 + 4) (two passes)
+};
+
 // Workgroup geometry a local pass is launched with.
 struct LocalLaunch {
     int threads;       // per workgroup
@@ -218,12 +234,13 @@ void set_last_error(const std::string &msg);
 // w_M^{-r} = exp(-2 pi i r / M) from the exact integer r, in FP64, rounded
 // once to FP32.
 float2 root_neg(int64_t r, int64_t M);
-// Stage twiddle factor tables of every on-chip length 2^1 .. 2^12,
+// Stage twiddle factor tables of every length 2^1 .. 2^kStageMaxLog2,
 // concatenated; off[l] is the first entry of length 2^l.
-bool stage_tables(std::vector<float2> &stw, int64_t off[kMaxOnChipLog2 + 1]);
+bool stage_tables(std::vector<float2> &stw, int64_t off[kStageMaxLog2 + 1]);
 // Phase-II tables of N = 2^lN: w_N^{-h*Lo} (hi), w_N^{-l} (lo) with
 // Lo = 2^middle_log2lo(lN), and the 128 x 128 tile table.
 constexpr int middle_log2lo(int lN) { return (lN + 1) / 2; }
+void top_tables(int lN, std::vector<float2> &hi, std::vector<float2> &lo);  // the first two
 void middle_tables(int lN, std::vector<float2> &hi, std::vector<float2> &lo, std::vector<float2> &tile);
 
 // Kernel tables of the split MFMA forms (local_fft_fp16x3.hip,
@@ -239,6 +256,13 @@ LocalLaunch local_fft_geometry(const LocalPass &p);
 hipError_t local_fft_prepare();  // raises the dynamic-LDS limit of every kernel once
 hipError_t launch_local_fft(const LocalPass &p, hipStream_t s);
 hipError_t launch_middle(const MiddlePass &p, hipStream_t s);
+// The direct form's split of N = 2^log2N (tables unset).
+DirectForm direct_form(int log2N);
+// Kernel launches of the form.
+constexpr int direct_launches(int log2N) { return log2N <= kDirectChipLog2 ? 1 : 2; }
+// The whole transform on stream s: in -> ws -> out (one workgroup: in -> out).
+// inverse: conj on load, conj times 1/N on store.
+hipError_t launch_direct(const DirectForm &f, const float2 *in, float2 *out, float2 *ws, bool inverse, hipStream_t s);
 // Pass 1 and pass 2 of the split form; hipErrorInvalidValue unless N1 is
 // 2^12, 2^13 or 2^14 and N2 is a multiple of 16.
 hipError_t launch_split_first(const SplitPass &p, hipStream_t s);

@@ -1,6 +1,7 @@
 // C ABI of the PACO library: validation, planning and execution on the
 // caller's stream.  Host code only; the kernels live in local_fft.hip and
 // middle.hip.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <mutex>
@@ -97,6 +98,8 @@ struct paco_plan_s {
     paco::SplitPass split_pass{};           // src/dst filled per execution
     bool sym = false;                       // N1 = N2 = 16 L: the symmetric split form (three passes)
     paco::SymPass sym_pass{};               // src/dst filled per execution
+    bool direct = false;                    // the direct form: one workgroup, or two column passes
+    paco::DirectForm direct_form{};
     paco_plan_s *inv = nullptr;             // N2 x N1 passes of the inverse (NULL: square, this plan's)
     void *scratch = nullptr;                // this device's scratch array (paco_execute_noalloc)
     std::string scratch_error;              // why scratch is NULL
@@ -277,10 +280,27 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
             paco::w16_operands(tw16.data());
         }
     }
-    int64_t stw_off[paco::kMaxOnChipLog2 + 1];
+    int64_t stw_off[paco::kStageMaxLog2 + 1];
     if (!paco::stage_tables(stw, stw_off)) {
         delete P;
         return fail(PACO_ERR_INVALID_ARG, "internal: stage twiddle layout mismatch");
+    }
+
+    // the direct form (direct.hip): FP32 up to 2^22 items, unless an option
+    // asks for another plan or the split form runs (N1 >= 2^12, see below)
+    const bool split_shape = (P->l1 == paco::kSplitLog2N1 || P->l1 == 13 || P->l1 == 14) && N2 >= 64;
+    const bool plain = !(opt.flags & ~PACO_PLAN_MIXED) && !opt.groups1 && !opt.groups3 && !opt.cols_long;
+    // (the split MFMA forms of lengths without a radix-16 stage run FP32 too)
+    const bool fp32 = dt == PACO_C64 || (P->l1 < 4 && P->l2 < 4);
+    P->direct = fp32 && plain && !split_shape && P->lN <= paco::kDirectMaxLog2;
+    std::vector<float2> tdw;
+    if (P->direct) {
+        P->direct_form = paco::direct_form(P->lN);
+        if (P->lN > paco::kDirectChipLog2) {
+            const int64_t n = int64_t(16) << P->direct_form.l1;
+            tdw.resize(size_t(n));
+            for (int64_t k = 0; k < n; ++k) tdw[k] = paco::root_neg(k, n);
+        }
     }
 
     // one device allocation, 256-byte aligned pieces
@@ -288,7 +308,8 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
     std::vector<Piece> pieces = {{tw.data(), tw.size() * 8, 0},       {thi.data(), thi.size() * 8, 0},
                                  {tlo.data(), tlo.size() * 8, 0},     {ttile.data(), ttile.size() * 8, 0},
                                  {stw.data(), stw.size() * 8, 0},     {tcw.data(), tcw.size() * 8, 0},
-                                 {tsj.data(), tsj.size() * 8, 0},     {tw16.data(), tw16.size() * 4, 0}};
+                                 {tsj.data(), tsj.size() * 8, 0},     {tw16.data(), tw16.size() * 4, 0},
+                                 {tdw.data(), tdw.size() * 8, 0}};
     size_t total = 0;
     for (auto &pc : pieces) {
         pc.off = total;
@@ -318,6 +339,16 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
     const float2 *d_tcw = reinterpret_cast<const float2 *>(at(5));
     const float2 *d_tsj = reinterpret_cast<const float2 *>(at(6));
     const float *d_tw16 = reinterpret_cast<const float *>(at(7));
+
+    if (P->direct) {
+        paco::DirectForm &f = P->direct_form;
+        f.stw1 = d_stw + stw_off[P->lN <= paco::kDirectChipLog2 ? std::min(P->lN, paco::kStageMaxLog2) : f.l1];
+        f.stw2 = d_stw + stw_off[f.l2];
+        f.hi = d_thi;
+        f.lo = d_tlo;
+        f.log2Lo = P->lLo;
+        f.cw = reinterpret_cast<const float2 *>(at(8));
+    }
 
     auto base_pass = [&](int64_t ld, int64_t ncols, int log2n) {
         LocalPass q{};
@@ -592,6 +623,14 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
                       P->phase3_two.log2n, 1 << P->phase3_two.log2T, (long long)g.tiles, g.threads, g.lds_bytes);
         desc += buf;
     }
+    if (P->direct) {
+        if (P->lN <= paco::kDirectChipLog2)
+            std::snprintf(buf, sizeof buf, " direct[one workgroup, 2^%d points]", P->lN);
+        else
+            std::snprintf(buf, sizeof buf, " direct[two column passes, 2^%d x 2^%d]", P->direct_form.l1,
+                          P->direct_form.l2);
+        desc += buf;
+    }
     if (P->s1 || P->s2) {
         std::snprintf(buf, sizeof buf, " mixed-radix[N1=%lld^%d*2^%d N2=%lld^%d*2^%d]", (long long)b, P->m1, P->s1,
                       (long long)b, P->m2, P->s2);
@@ -627,7 +666,9 @@ paco_status create_with_inverse(paco_plan **plan, int64_t N1, int64_t N2, int64_
     if (opt.cols_long < 0 || (opt.cols_long > 0 && ilog2_exact(opt.cols_long) < 0))
         return fail(PACO_ERR_INVALID_ARG, "cols_long must be 0 (default) or a power of two");
     paco_status st = create_impl(plan, N1, N2, p, b, dt, opt);
-    if (st != PACO_OK || N1 == N2) return st;  // square: the inverse reuses the forward passes
+    // square shapes and the direct form (whose split of N is its own): the
+    // inverse reuses the forward passes
+    if (st != PACO_OK || N1 == N2 || (*plan)->direct) return st;
     const std::string note = g_last_error;
     paco_plan *inv = nullptr;
     st = create_impl(&inv, N2, N1, p, b, dt, opt);
@@ -679,7 +720,9 @@ paco_status paco_plan_describe(const paco_plan *plan, int32_t *launches, char *b
 {
     if (!plan) return fail(PACO_ERR_INVALID_ARG, "plan is NULL");
     if (launches)  // the split form runs its two passes in place of Phase I's passes and Phase II
-        *launches = plan->sym ? 3 : int32_t((plan->split ? 2 : plan->phase1.size() + 1) + plan->phase3.size());
+        *launches = plan->direct ? paco::direct_launches(plan->lN)
+                    : plan->sym  ? 3
+                                 : int32_t((plan->split ? 2 : plan->phase1.size() + 1) + plan->phase3.size());
     if (buf && buflen) {
         std::strncpy(buf, plan->desc.c_str(), buflen - 1);
         buf[buflen - 1] = 0;
@@ -772,6 +815,11 @@ paco_status run_sym(const paco_plan *plan, int pass, const void *src, void *dst,
 // 1/N on Phase III's stores, i.e. conj(Omega conj(in)) / N.
 paco_status run_three(const paco_plan *plan, const void *in, void *out, void *workspace, hipStream_t s, bool inverse)
 {
+    if (plan->direct) {
+        hipError_t e = paco::launch_direct(plan->direct_form, static_cast<const float2 *>(in), static_cast<float2 *>(out),
+                                           static_cast<float2 *>(workspace), inverse, s);
+        return e == hipSuccess ? PACO_OK : hip_fail(e, "direct form launch");
+    }
     if (plan->sym) {
         paco_status st = run_sym(plan, 1, in, workspace, inverse, s);
         if (st == PACO_OK) st = run_sym(plan, 2, workspace, out, inverse, s);

@@ -1,5 +1,5 @@
-// Device code shared by the LocalFFT kernels (local_fft.hip) and the batched
-// persistent kernel (batch.hip): radix-16 Stockham stages with LDS
+// Device code of the LocalFFT kernels (local_fft.hip), shared with the direct
+// form and the batched kernel (tile.h): radix-16 Stockham stages with LDS
 // exchanges, the HBM-boundary row maps of Lemma 1, and one column tile of a
 // single-pass local transform.  Included once per translation unit.
 #pragma once
@@ -90,10 +90,6 @@ __device__ __forceinline__ void st2_stream(void *p, float2 v)
     __builtin_nontemporal_store(t, reinterpret_cast<sf2 *>(p));
 }
 
-// HBM stores of a tile's results.  COH: a device-coherent store (written
-// through this XCD's L2), for results another workgroup of the same launch
-// reads after a completion counter says they are there; the 16-byte form
-// becomes two such 8-byte stores.
 // Loads of data the transform never reads again (Phase II's source buffer):
 // non-temporal, so they do not push out of the caches the lines just written
 // for the next phase (on a 2^24 transform, whose three 128 MB buffers
@@ -113,6 +109,9 @@ __device__ __forceinline__ float4 ld4_last(const float2 *p)
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
+// Store of an item.  COH: a device-coherent store (written through this
+// XCD's L2), for results another workgroup of the same launch reads after a
+// completion counter says they are there.
 template <bool COH>
 __device__ __forceinline__ void st2(char *p, float2 v)
 {
@@ -124,17 +123,6 @@ __device__ __forceinline__ void st2(char *p, float2 v)
         *reinterpret_cast<float2 *>(p) = v;
     }
 }
-template <bool COH>
-__device__ __forceinline__ void st4(char *p, float4 v)
-{
-    if constexpr (COH) {
-        st2<true>(p, make_float2(v.x, v.y));
-        st2<true>(p + 8, make_float2(v.z, v.w));
-    } else {
-        *reinterpret_cast<float4 *>(p) = v;
-    }
-}
-
 // LDS index with 4 pad items per 64: the radix-16 first-stage writes (row
 // stride 16*T items) land on distinct banks.
 __device__ __forceinline__ int lpad(int e) { return e + ((e >> 6) << 2); }
@@ -148,7 +136,6 @@ struct Ctx {
     uint32_t orow_out, k_out;  // generic: output row = orow_out + pi_out(k) * k_out
     int out_t, out_ell;
     int out_s = 0;             // generic: short top digit of pi_out (mixed radix)
-    bool act;                  // runtime tile width: this thread owns butterflies (tid < nt)
     float oscale = 0.f;        // nonzero: every output is stored as conj(y) * oscale
     bool stream = false;       // MODE 2: streaming stores (st2_stream)
 };
@@ -453,7 +440,7 @@ __device__ __forceinline__ void mfma_dft16(float2 *u, float2 *scr, int lane)
 // reversed output rows (Phase I), 1 natural output rows (Phase III), 2 the
 // transposed natural output (row = column, n items per row; Phase I of the
 // fused pipeline).
-template <int LOG2N, int S, int EG, int LT, int MODE, int TB, bool GEN, int H, bool COH = false, int PREC = kPrecFP32>
+template <int LOG2N, int S, int EG, int LT, int MODE, int TB, bool GEN, int H, int PREC = kPrecFP32>
 __device__ __forceinline__ void run_stage(float2 (&v)[H * EG], const Ctx &c)
 {
     constexpr int LR = stage_log2radix(LOG2N, S);
@@ -464,10 +451,6 @@ __device__ __forceinline__ void run_stage(float2 (&v)[H * EG], const Ctx &c)
     const int log2T = LT >= 0 ? LT : c.log2T;
     const int nt = LT >= 0 ? ((1 << (LOG2N + (LT >= 0 ? LT : 0))) / EG) : c.nt;
     const int Tm = (1 << log2T) - 1;
-    // with a compile-time tile width every thread of the workgroup owns
-    // butterflies; with a runtime one the threads from nt on only take part
-    // in the barriers
-    const bool act = LT >= 0 || c.act;
     // radix-16 stages of the split-precision forms run on MFMA
     constexpr bool MF = PREC != kPrecFP32 && LR == 4;
 
@@ -515,33 +498,28 @@ __device__ __forceinline__ void run_stage(float2 (&v)[H * EG], const Ctx &c)
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             if (S > 0 || h > 0 || MF) __syncthreads();  // the previous LDS contents were consumed
-            if (act) {
 #pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int g = c.tid + i * nt;
-                    const int t = g & Tm, j = g >> log2T;
-                    const int idxD = ((j >> LNS) << (LNS + LR)) + (j & ((1 << LNS) - 1));
+            for (int i = 0; i < NB; ++i) {
+                const int g = c.tid + i * nt;
+                const int t = g & Tm, j = g >> log2T;
+                const int idxD = ((j >> LNS) << (LNS + LR)) + (j & ((1 << LNS) - 1));
 #pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        c.lds[lpad(((idxD + (r << LNS)) << log2T) + t)] = v[h * EG + i * R + r];
-                }
+                for (int r = 0; r < R; ++r)
+                    c.lds[lpad(((idxD + (r << LNS)) << log2T) + t)] = v[h * EG + i * R + r];
             }
             __syncthreads();
-            if (act) {
 #pragma unroll
-                for (int i = 0; i < NB2; ++i) {
-                    const int g = c.tid + i * nt;
-                    const int t = g & Tm, j = g >> log2T;
+            for (int i = 0; i < NB2; ++i) {
+                const int g = c.tid + i * nt;
+                const int t = g & Tm, j = g >> log2T;
 #pragma unroll
-                    for (int r = 0; r < R2; ++r)
-                        v[h * EG + i * R2 + r] = c.lds[lpad(((j + (r << LNR2)) << log2T) + t)];
-                }
+                for (int r = 0; r < R2; ++r)
+                    v[h * EG + i * R2 + r] = c.lds[lpad(((j + (r << LNR2)) << log2T) + t)];
             }
         }
-        run_stage<LOG2N, S + 1, EG, LT, MODE, TB, GEN, H, COH, PREC>(v, c);
+        run_stage<LOG2N, S + 1, EG, LT, MODE, TB, GEN, H, PREC>(v, c);
     } else {
         // last stage: j < n/R = 2^LNS, outputs are the natural-order rows k = j + r*2^LNS.
-        if (!act) return;
         if (c.oscale != 0.f) {
 #pragma unroll
             for (int k = 0; k < H * EG; ++k) v[k] = conj_scale(v[k], c.oscale);
@@ -562,7 +540,7 @@ __device__ __forceinline__ void run_stage(float2 (&v)[H * EG], const Ctx &c)
                 for (int r = 0; r < R; ++r) {
                     const uint32_t row_off = MODE == 0 ? uint32_t(crev(r, TB, LR / TB)) * c.ld8 : (uint32_t(r) << LNS) * c.ld8;
                     const float2 a0 = v[i * R + r], a1 = v[EG + i * R + r];
-                    st4<COH>(c.dst + base + row_off, make_float4(a0.x, a0.y, a1.x, a1.y));
+                    *reinterpret_cast<float4 *>(c.dst + base + row_off) = make_float4(a0.x, a0.y, a1.x, a1.y);
                 }
             }
             return;
@@ -579,7 +557,7 @@ __device__ __forceinline__ void run_stage(float2 (&v)[H * EG], const Ctx &c)
                     const uint32_t base = ((drev<TB, LNS / TB>(j) << LR) * c.ld8) + uint32_t(t) * 8u;
 #pragma unroll
                     for (int r = 0; r < R; ++r)
-                        st2<COH>(c.dst + base + uint32_t(crev(r, TB, LR / TB)) * c.ld8, u[r]);
+                        st2<false>(c.dst + base + uint32_t(crev(r, TB, LR / TB)) * c.ld8, u[r]);
                 } else if constexpr (MODE == 2) {
                     // transposed output: row (col0 + t) holds all n frequencies in order
                     const uint32_t base = (uint32_t(t) << (LOG2N + 3)) + uint32_t(j) * 8u;
@@ -588,20 +566,20 @@ __device__ __forceinline__ void run_stage(float2 (&v)[H * EG], const Ctx &c)
                         if (c.stream)
                             st2_stream(c.dst + base + (uint32_t(r) << (LNS + 3)), u[r]);
                         else
-                            st2<COH>(c.dst + base + (uint32_t(r) << (LNS + 3)), u[r]);
+                            st2<false>(c.dst + base + (uint32_t(r) << (LNS + 3)), u[r]);
                     }
                 } else if constexpr (MODE == 1) {
                     const uint32_t base = uint32_t(j) * c.ld8 + uint32_t(t) * 8u;
 #pragma unroll
                     for (int r = 0; r < R; ++r)
-                        st2<COH>(c.dst + base + (uint32_t(r) << LNS) * c.ld8, u[r]);
+                        st2<false>(c.dst + base + (uint32_t(r) << LNS) * c.ld8, u[r]);
                 } else {
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
                         const uint32_t k = j + (r << LNS);
                         const uint32_t m = uint32_t(digmap<GEN>(k, c.out_t, c.out_ell, c.out_s, true));
                         const uint32_t off = (c.orow_out + m * c.k_out) * c.ld8 + uint32_t(t) * 8u;
-                        st2<COH>(c.dst + off, u[r]);
+                        st2<false>(c.dst + off, u[r]);
                     }
                 }
             }
@@ -651,12 +629,12 @@ struct TopTw {
 // traffic and arithmetic.
 // EG = 32 (with H = 2) doubles the tile width: 512 threads hold 64 items
 // each (two waves per SIMD, 256 VGPRs of budget).
-// COH: device-coherent result stores (see st2).  PREC: arithmetic of the
+// PREC: arithmetic of the
 // radix-16 butterflies (FP32 VALU, or one of the split MFMA forms).
 // LT = log2 of the tile's columns; the caller launches exactly
 // 2^(LOG2N + LT - (H == 2)) / EG threads per tile.  srcm/dstm: the matrix
 // (row length ld items); col0: the tile's first column.
-template <int LOG2N, int MODE, int TB, int H, int EG, int LT, bool COH = false, int PREC = kPrecFP32>
+template <int LOG2N, int MODE, int TB, int H, int EG, int LT, int PREC = kPrecFP32>
 __device__ __forceinline__ void fast_tile(const float2 *srcm, float2 *dstm, uint32_t ld, int64_t col0,
                                           const float2 *stw, float2 *smem, int tid, const TopTw *top = nullptr,
                                           bool conj_in = false, float oscale = 0.f, bool stream_out = false)
@@ -734,10 +712,9 @@ __device__ __forceinline__ void fast_tile(const float2 *srcm, float2 *dstm, uint
     c.k_out = 1;
     c.out_t = 0;
     c.out_ell = 0;
-    c.act = true;
     c.oscale = oscale;
     c.stream = stream_out;
-    run_stage<LOG2N, 0, EG, LTG, MODE == 3 ? 1 : (MODE == 4 ? 2 : MODE), TB, false, H, COH, PREC>(v, c);
+    run_stage<LOG2N, 0, EG, LTG, MODE == 3 ? 1 : (MODE == 4 ? 2 : MODE), TB, false, H, PREC>(v, c);
 }
 
 // One column tile of a single-pass transform of n = 16^s points (s <= 3)

@@ -14,11 +14,11 @@ float2 root_neg(int64_t r, int64_t M)
     return make_float2(float(std::cos(a)), float(-std::sin(a)));
 }
 
-bool stage_tables(std::vector<float2> &stw, int64_t off[kMaxOnChipLog2 + 1])
+bool stage_tables(std::vector<float2> &stw, int64_t off[kStageMaxLog2 + 1])
 {
     stw.clear();
     off[0] = 0;
-    for (int l = 1; l <= kMaxOnChipLog2; ++l) {
+    for (int l = 1; l <= kStageMaxLog2; ++l) {
         off[l] = int64_t(stw.size());
         for (int S = 1; S < stage_count(l); ++S) {
             const int R = 1 << stage_log2radix(l, S);
@@ -35,17 +35,23 @@ bool stage_tables(std::vector<float2> &stw, int64_t off[kMaxOnChipLog2 + 1])
     return true;
 }
 
-void middle_tables(int lN, std::vector<float2> &hi, std::vector<float2> &lo, std::vector<float2> &tile)
+void top_tables(int lN, std::vector<float2> &hi, std::vector<float2> &lo)
 {
     const int64_t N = int64_t(1) << lN;
     const int lLo = middle_log2lo(lN);
     const int64_t Lo = int64_t(1) << lLo, Hi = N >> lLo;
-    constexpr int64_t TT = kTwTile;
     hi.resize(Hi);
     lo.resize(Lo);
-    tile.resize(TT * TT);
     for (int64_t h = 0; h < Hi; ++h) hi[h] = root_neg(h * Lo, N);
     for (int64_t l = 0; l < Lo; ++l) lo[l] = root_neg(l, N);
+}
+
+void middle_tables(int lN, std::vector<float2> &hi, std::vector<float2> &lo, std::vector<float2> &tile)
+{
+    const int64_t N = int64_t(1) << lN;
+    constexpr int64_t TT = kTwTile;
+    top_tables(lN, hi, lo);
+    tile.resize(TT * TT);
     for (int64_t i = 0; i < TT; ++i)
         for (int64_t j = 0; j < TT; ++j) tile[i * TT + j] = root_neg((i * j) % N, N);
 }
