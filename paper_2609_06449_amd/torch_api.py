@@ -17,8 +17,16 @@ def get_plan(N1: int, N2: int, p: int, b: int, dt: int = paco.PACO_C64, mixed: b
     return plan
 
 
+# The current device's current stream.  torch.cuda.current_stream() builds a
+# Stream object, 2.7 us of the 7.7 us a small transform took on the host; the
+# raw handle takes 0.1 us (the object stays the way where torch lacks the call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check_tensor(x: torch.Tensor, n: int, name: str):

@@ -127,3 +127,21 @@ def test_graph_replays_equal_eager():
             g.replay()
             torch.cuda.synchronize()
             assert np.array_equal(_bits(out.cpu().numpy()), _bits(eager)), (k, rep)
+
+
+def test_torch_calls_run_on_the_current_stream():
+    from paper_2609_06449_amd import torch_api as ta
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+    assert len({s.cuda_stream for s in streams}) == 3
+    x = _dev(inputs.normal(1 << 13, seed=400))
+    for s in streams:
+        with torch.cuda.stream(s):
+            assert ta._stream() == s.cuda_stream == torch.cuda.current_stream().cuda_stream
+            # ordered behind the stream's own work: the copy is slow, the transform reads its result
+            big = torch.zeros(1 << 26, dtype=torch.float32, device="cuda")
+            y = x.clone()
+            big.add_(1.0)
+            y.mul_(big[0])
+            out = ta.fft(y, 128, 64, 4, 2)
+        torch.cuda.synchronize()
+        assert oracle.rel_l2(out.cpu().numpy(), oracle.dft(x.cpu().numpy())) <= TOL
