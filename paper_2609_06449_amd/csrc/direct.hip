@@ -1,4 +1,4 @@
-// The direct form of a single FP32 transform of at most 2^22 items: one
+// The direct form of a single FP32 transform of at most 2^23 items: one
 // workgroup up to 2^14 items, two column passes above (tile.h).
 //
 // At these sizes a call is launches and latency, not bytes: the phases' three
@@ -44,28 +44,33 @@ __global__ __launch_bounds__(512) void direct_chip14_kernel(DirectArgs P)
 // against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
 // 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
 constexpr int kLT = 2;
+// 4096-point columns (2^23 only): two LDS groups of two columns, 64 KiB, so
+// two workgroups share a CU.  2^23: 90 us; the three-pass forms it replaces
+// took 95 to 130 by shape.  2^24 in two passes took 191 us against 162 for the
+// symmetric form's three, which ends the range.
+constexpr int groups(int l) { return l == 12 ? 2 : 1; }
 
 template <int L>
-__global__ __launch_bounds__(tile_threads(L, kLT, 1)) void direct_a_kernel(DirectArgs P)
+__global__ __launch_bounds__(tile_threads(L, kLT, groups(L))) void direct_a_kernel(DirectArgs P)
 {
-    __shared__ float2 smem[tile_lds(L, kLT, 1)];
-    pass_a_tile<L, kLT, 1, false>(P.src, P.dst, P.l2, kLT, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.stw,
+    __shared__ float2 smem[tile_lds(L, kLT, groups(L))];
+    pass_a_tile<L, kLT, groups(L), false>(P.src, P.dst, P.l2, kLT, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.stw,
                                   smem, threadIdx.x, P.conj_in != 0);
 }
 
 template <int L>
-__global__ __launch_bounds__(tile_threads(L, kLT, 1)) void direct_b_kernel(DirectArgs P)
+__global__ __launch_bounds__(tile_threads(L, kLT, groups(L))) void direct_b_kernel(DirectArgs P)
 {
-    __shared__ float2 smem[tile_lds(L, kLT, 1)];
-    pass_b_tile<L, kLT, 1>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.top, P.stw, smem,
+    __shared__ float2 smem[tile_lds(L, kLT, groups(L))];
+    pass_b_tile<L, kLT, groups(L)>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.top, P.stw, smem,
                            threadIdx.x, P.out_scale);
 }
 
 template <int L>
 void launch_pass(bool b, unsigned tiles, const DirectArgs &a, hipStream_t s)
 {
-    if (b) hipLaunchKernelGGL(direct_b_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, 1)), 0, s, a);
-    else hipLaunchKernelGGL(direct_a_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, 1)), 0, s, a);
+    if (b) hipLaunchKernelGGL(direct_b_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, groups(L))), 0, s, a);
+    else hipLaunchKernelGGL(direct_a_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, groups(L))), 0, s, a);
 }
 
 // one pass of 2^l points over 2^lcols columns
@@ -78,6 +83,7 @@ hipError_t pass(bool b, int l, int lcols, const DirectArgs &a, hipStream_t s)
     case 9: launch_pass<9>(b, tiles, a, s); break;
     case 10: launch_pass<10>(b, tiles, a, s); break;
     case 11: launch_pass<11>(b, tiles, a, s); break;
+    case 12: launch_pass<12>(b, tiles, a, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -206,12 +206,12 @@ struct SymPass {
     uint32_t resident2;             // pass 2 of the wide form (N2 = 2^15), likewise
 };
 
-// The direct form (direct.hip), FP32, N <= 2^22: one launch of one workgroup
+// The direct form (direct.hip), FP32, N <= 2^23: one launch of one workgroup
 // up to 2^14 items, else two column passes over N = 2^l1 2^l2 (tile.h).  The
 // split of N is the library's own: neither N1 x N2 nor b nor p of the plan
 // enters the result.
 constexpr int kDirectChipLog2 = 14;  // the largest transform of one workgroup
-constexpr int kDirectMaxLog2 = 22;
+constexpr int kDirectMaxLog2 = 23;
 struct DirectForm {
     int32_t log2N, l1, l2;           // two passes: pass A 2^l1 points over 2^l2 columns, pass B the reverse
     const float2 *stw1, *stw2;       // stage tables of the two lengths (one workgroup: stw1)

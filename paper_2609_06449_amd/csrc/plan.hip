@@ -100,7 +100,8 @@ struct paco_plan_s {
     paco::SymPass sym_pass{};               // src/dst filled per execution
     bool direct = false;                    // the direct form: one workgroup, or two column passes
     paco::DirectForm direct_form{};
-    paco_plan_s *inv = nullptr;             // N2 x N1 passes of the inverse (NULL: square, this plan's)
+    paco_plan_s *fwd = nullptr;             // the balanced shape's passes, which paco_execute runs (NULL: this plan's)
+    paco_plan_s *inv = nullptr;             // passes of the inverse (NULL: this plan's, or fwd's)
     void *scratch = nullptr;                // this device's scratch array (paco_execute_noalloc)
     std::string scratch_error;              // why scratch is NULL
     std::string inv_error;                  // non-empty: the inverse passes could not be built
@@ -286,13 +287,15 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
         return fail(PACO_ERR_INVALID_ARG, "internal: stage twiddle layout mismatch");
     }
 
-    // the direct form (direct.hip): FP32 up to 2^22 items, unless an option
-    // asks for another plan or the split form runs (N1 >= 2^12, see below)
+    // the direct form (direct.hip): FP32 up to 2^23 items, unless an option
+    // asks for another plan, or the split form runs at up to 2^20 items (there
+    // its stage hooks are the passes of paco_execute)
     const bool split_shape = (P->l1 == paco::kSplitLog2N1 || P->l1 == 13 || P->l1 == 14) && N2 >= 64;
     const bool plain = !(opt.flags & ~PACO_PLAN_MIXED) && !opt.groups1 && !opt.groups3 && !opt.cols_long;
     // (the split MFMA forms of lengths without a radix-16 stage run FP32 too)
     const bool fp32 = dt == PACO_C64 || (P->l1 < 4 && P->l2 < 4);
-    P->direct = fp32 && plain && !split_shape && P->lN <= paco::kDirectMaxLog2;
+    P->direct = fp32 && plain && !(split_shape && P->lN <= 20) &&
+                P->lN <= paco::kDirectMaxLog2;
     std::vector<float2> tdw;
     if (P->direct) {
         P->direct_form = paco::direct_form(P->lN);
@@ -666,10 +669,33 @@ paco_status create_with_inverse(paco_plan **plan, int64_t N1, int64_t N2, int64_
     if (opt.cols_long < 0 || (opt.cols_long > 0 && ilog2_exact(opt.cols_long) < 0))
         return fail(PACO_ERR_INVALID_ARG, "cols_long must be 0 (default) or a power of two");
     paco_status st = create_impl(plan, N1, N2, p, b, dt, opt);
-    // square shapes and the direct form (whose split of N is its own): the
-    // inverse reuses the forward passes
-    if (st != PACO_OK || N1 == N2 || (*plan)->direct) return st;
+    if (st != PACO_OK || (*plan)->direct) return st;  // (the direct form's split of N is its own)
     const std::string note = g_last_error;
+    // FP32 from 2^24 items on: the balanced shape of N runs the symmetric
+    // form's three passes, which no other shape beats.  Shapes without that
+    // form take its passes, and so does the inverse of non-square ones (on one
+    // HBM every shape is a view of the same vector).  us before / after:
+    // 1024 x 16384 232 / 162, 2048 x 16384 470 / 322, 2048 x 32768 986 / 657;
+    // inverses 4096 x 16384 777 / 655, 8192 x 32768 5300 / 2960 (its 32768 x
+    // 8192 passes were five).  Plan options that ask for a form keep the
+    // shape's own passes.
+    const int lN = (*plan)->lN;
+    const bool plain = !(opt.flags & ~PACO_PLAN_MIXED) && !opt.groups1 && !opt.groups3 && !opt.cols_long;
+    paco_plan *best = nullptr;
+    if (dt == PACO_C64 && plain && lN >= 24 && !((*plan)->sym && N1 == N2)) {
+        paco_plan_options o{};
+        if (create_impl(&best, int64_t(1) << (lN / 2), int64_t(1) << (lN - lN / 2), 2, 2, dt, o) != PACO_OK) best = nullptr;
+        g_last_error = note;
+    }
+    if (best && !(*plan)->sym) {
+        (*plan)->fwd = best;  // the inverse runs it too
+        return PACO_OK;
+    }
+    if (best) {
+        (*plan)->inv = best;
+        return PACO_OK;
+    }
+    if (N1 == N2) return st;  // square: the inverse reuses the forward passes
     paco_plan *inv = nullptr;
     st = create_impl(&inv, N2, N1, p, b, dt, opt);
     if (st != PACO_OK) {
@@ -720,11 +746,13 @@ paco_status paco_plan_describe(const paco_plan *plan, int32_t *launches, char *b
 {
     if (!plan) return fail(PACO_ERR_INVALID_ARG, "plan is NULL");
     if (launches)  // the split form runs its two passes in place of Phase I's passes and Phase II
-        *launches = plan->direct ? paco::direct_launches(plan->lN)
-                    : plan->sym  ? 3
-                                 : int32_t((plan->split ? 2 : plan->phase1.size() + 1) + plan->phase3.size());
+        *launches = plan->fwd      ? 3
+                    : plan->direct ? paco::direct_launches(plan->lN)
+                    : plan->sym    ? 3
+                                   : int32_t((plan->split ? 2 : plan->phase1.size() + 1) + plan->phase3.size());
     if (buf && buflen) {
-        std::strncpy(buf, plan->desc.c_str(), buflen - 1);
+        const std::string d = plan->fwd ? plan->desc + " | executes " + plan->fwd->desc : plan->desc;
+        std::strncpy(buf, d.c_str(), buflen - 1);
         buf[buflen - 1] = 0;
     }
     return PACO_OK;
@@ -734,6 +762,7 @@ paco_status paco_plan_destroy(paco_plan *plan)
 {
     if (!plan) return PACO_OK;
     if (plan->inv) paco_plan_destroy(plan->inv);
+    if (plan->fwd) paco_plan_destroy(plan->fwd);
     if (plan->dev_tables) (void)hipFree(plan->dev_tables);
     delete plan;
     return PACO_OK;
@@ -855,7 +884,7 @@ paco_status paco_execute(const paco_plan *plan, const void *in, void *out, void 
 {
     paco_status st = check_buffers(plan, in, out, workspace, workspace_bytes);
     if (st != PACO_OK) return st;
-    return run_three(plan, in, out, workspace, static_cast<hipStream_t>(stream), false);
+    return run_three(plan->fwd ? plan->fwd : plan, in, out, workspace, static_cast<hipStream_t>(stream), false);
 }
 
 paco_status paco_execute_noalloc(const paco_plan *plan, const void *in, void *out, void *stream)
@@ -875,7 +904,7 @@ paco_status paco_execute_inverse(const paco_plan *plan, const void *in, void *ou
     paco_status st = check_buffers(plan, in, out, workspace, workspace_bytes);
     if (st != PACO_OK) return st;
     if (!plan->inv_error.empty()) return fail(PACO_ERR_UNSUPPORTED, plan->inv_error);
-    return run_three(plan->inv ? plan->inv : plan, in, out, workspace, static_cast<hipStream_t>(stream), true);
+    return run_three(plan->inv ? plan->inv : plan->fwd ? plan->fwd : plan, in, out, workspace, static_cast<hipStream_t>(stream), true);
 }
 
 paco_status paco_execute_two_pass(const paco_plan *plan, const void *in, void *out, void *workspace,

@@ -1,4 +1,4 @@
-"""The direct form (FP32, N <= 2^22: one workgroup up to 2^14 items, two column
+"""The direct form (FP32, N <= 2^23: one workgroup up to 2^14 items, two column
 passes above) on the GPU: every length of its range against the FP64 oracle,
 forward and inverse, in place, the same bits for every shape, base and slab
 count of a length, the batched kernel's same bits (partly filled tasks, both
@@ -41,7 +41,7 @@ def _balanced(k):
     return 1 << l1, 1 << (k - l1)
 
 
-@pytest.mark.parametrize("k", range(2, 23))
+@pytest.mark.parametrize("k", range(2, 24))
 def test_every_length_forward_inverse_in_place(k):
     N1, N2 = _balanced(k)
     plan = paco.Plan(N1, N2, 2, 2)
@@ -63,7 +63,8 @@ def test_every_length_forward_inverse_in_place(k):
     (13, [(2, 4096, 2, 2, False), (2048, 4, 4, 2, False), (128, 64, 4, 16, True)]),
     (14, [(16, 1024, 2, 4, False), (128, 128, 16, 16, True)]),
     (17, [(2, 1 << 16, 2, 2, False), (512, 256, 4, 2, False), (64, 2048, 4, 16, True)]),
-    (22, [(64, 1 << 16, 16, 4, False), (2048, 2048, 64, 2, False), (1024, 4096, 16, 16, True)]),
+    (22, [(64, 1 << 16, 16, 4, False), (2048, 2048, 64, 2, False), (4096, 1024, 16, 4, False)]),
+    (23, [(4096, 2048, 16, 16, True), (1 << 13, 1024, 16, 2, False)]),
 ])
 def test_same_bits_for_every_shape_base_and_slab_count(k, shapes):
     x = _dev(inputs.normal(1 << k, seed=200 + k))
@@ -80,7 +81,7 @@ def test_options_and_split_shapes_keep_their_plans():
     assert " direct[" not in paco.Plan(64, 64, 4, 4, groups1=1).description
     assert " direct[" not in paco.Plan(4096, 64, 4, 4).description
     assert " direct[" not in paco.Plan(64, 64, 4, 4, paco.PACO_C64_MFMA_FP16X3).description
-    assert " direct[" not in paco.Plan(2048, 4096, 4, 2, mixed=True).description  # 2^23
+    assert " direct[" not in paco.Plan(4096, 4096, 4, 2).description
 
 
 @pytest.mark.parametrize("queue", [0, paco.PACO_BATCH_ONE_QUEUE])
