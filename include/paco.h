@@ -350,7 +350,7 @@ typedef struct {
     uint32_t spin_limit;   /* 0: default (2^22); polls before a completion wait
                               gives up and is counted by paco_batch_errors          */
     int64_t gap;           /* with PACO_BATCH_SET_GAP: tiles between a job and its
-                              successor in a queue (default: 4 x the resident
+                              successor in a queue (default: 2 x the resident
                               workgroups per queue)                                  */
 } paco_batch_options;
 

@@ -107,45 +107,87 @@ struct BatchArgs {
 __device__ __forceinline__ int own(int tid) { return int(opaque(uint32_t(tid))); }
 
 constexpr int pass_lt(int l) { return kTileLog2 - l; }
-// transforms of 2^l points a small task holds: 16 items per thread (shorter
-// ones: one transform per thread)
-constexpr int small_lt(int l) { return l < 4 ? 9 : 13 - l; }
+// transforms of 2^l points a small task of 2^lw threads holds: 16 items per
+// thread (shorter ones: one transform per thread)
+constexpr int small_lt(int l, int lw) { return l < 4 ? lw : lw + 4 - l; }
+constexpr int kLogBT = 9;      // the persistent kernel's threads
+static_assert(kBT == 1 << kLogBT, "threads per workgroup");
+// Batches without a transform of two passes need no work queue: a plain
+// launch of one workgroup per task (batch_small_kernel), 256 threads and four
+// workgroups per CU up to 2^12 items per transform, else 512 threads.
+// 8192 transforms of 2^6..2^12: 38 us, through the queue 59, and 162 with one
+// transform per workgroup and three phases through L2 (a copy takes 29).
+constexpr int kLogST = 8, kShortMaxLog2 = 12;
 
 constexpr int batch_lds()
 {
     int m = tile_lds(13, 1, 2);  // kOne
-    for (int l = kBatchMinLog2; l <= 13; ++l) m = m < tile_lds(l, small_lt(l), 1) ? tile_lds(l, small_lt(l), 1) : m;
+    for (int l = kBatchMinLog2; l <= 13; ++l) m = m < tile_lds(l, small_lt(l, kLogBT), 1) ? tile_lds(l, small_lt(l, kLogBT), 1) : m;
     for (int l = kPassMin; l <= kPassMax; ++l) m = m < tile_lds(l, pass_lt(l), 2) ? tile_lds(l, pass_lt(l), 2) : m;
     return m;
 }
 static_assert(2 * (batch_lds() * 8 + 16) <= 160 * 1024, "two workgroups per CU");
 
-template <int L>
+constexpr int plain_lds(int lw)
+{
+    if (lw == kLogBT) return batch_lds();
+    int m = 0;
+    for (int l = kBatchMinLog2; l <= kShortMaxLog2; ++l)
+        m = m < tile_lds(l, small_lt(l, lw), 1) ? tile_lds(l, small_lt(l, lw), 1) : m;
+    return m;
+}
+static_assert(4 * plain_lds(kLogST) * 8 <= 160 * 1024, "four workgroups per CU");
+
+template <int L, int LW>
 __device__ __forceinline__ void run_small_len(const BatchArgs &A, const BatchJob &J, float2 *smem, int tid)
 {
-    static_assert(tile_threads(L, small_lt(L), 1) == kBT, "tile geometry");
+    static_assert(tile_threads(L, small_lt(L, LW), 1) == 1 << LW, "tile geometry");
     const int64_t *m = A.members + J.base;
     const int n = J.count;
-    chip_tile<L, small_lt(L)>(A.in, A.out, [&](int t) { return t < n ? m[t] : int64_t(-1); }, A.stw + A.stw_off[L], smem,
-                              own(tid), false, 0.f);
+    chip_tile<L, small_lt(L, LW)>(A.in, A.out, [&](int t) { return t < n ? m[t] : int64_t(-1); }, A.stw + A.stw_off[L],
+                                  smem, own(tid), false, 0.f);
 }
 
+template <int LW>
 __device__ __forceinline__ void run_small(const BatchArgs &A, const BatchJob &J, float2 *smem, int tid)
 {
     switch (J.l1) {
-    case 2: run_small_len<2>(A, J, smem, tid); break;
-    case 3: run_small_len<3>(A, J, smem, tid); break;
-    case 4: run_small_len<4>(A, J, smem, tid); break;
-    case 5: run_small_len<5>(A, J, smem, tid); break;
-    case 6: run_small_len<6>(A, J, smem, tid); break;
-    case 7: run_small_len<7>(A, J, smem, tid); break;
-    case 8: run_small_len<8>(A, J, smem, tid); break;
-    case 9: run_small_len<9>(A, J, smem, tid); break;
-    case 10: run_small_len<10>(A, J, smem, tid); break;
-    case 11: run_small_len<11>(A, J, smem, tid); break;
-    case 12: run_small_len<12>(A, J, smem, tid); break;
-    default: run_small_len<13>(A, J, smem, tid); break;
+    case 2: run_small_len<2, LW>(A, J, smem, tid); break;
+    case 3: run_small_len<3, LW>(A, J, smem, tid); break;
+    case 4: run_small_len<4, LW>(A, J, smem, tid); break;
+    case 5: run_small_len<5, LW>(A, J, smem, tid); break;
+    case 6: run_small_len<6, LW>(A, J, smem, tid); break;
+    case 7: run_small_len<7, LW>(A, J, smem, tid); break;
+    case 8: run_small_len<8, LW>(A, J, smem, tid); break;
+    case 9: run_small_len<9, LW>(A, J, smem, tid); break;
+    case 10: run_small_len<10, LW>(A, J, smem, tid); break;
+    case 11: run_small_len<11, LW>(A, J, smem, tid); break;
+    case 12: run_small_len<12, LW>(A, J, smem, tid); break;
+    default:
+        if constexpr (LW >= kLogBT) run_small_len<13, LW>(A, J, smem, tid);
+        break;
     }
+}
+
+__device__ __forceinline__ void run_one(const BatchArgs &A, const BatchJob &J, float2 *smem, int tid)
+{
+    const TopRoots T = A.tabs[J.tab];
+    chip14_tile(A.in + J.base, A.out + J.base, A.stw + A.stw_off[13], T.hi, T.lo, smem, own(tid), false, 0.f);
+}
+
+// A batch of transforms of one workgroup: workgroup i runs task i.
+template <int LW>
+__global__ __launch_bounds__(1 << LW) void batch_small_kernel(BatchArgs A)
+{
+    __shared__ float2 smem[plain_lds(LW)];
+    const BatchJob &J = A.jobs[blockIdx.x];
+    if constexpr (LW >= kLogBT) {
+        if (J.kind == kOne) {
+            run_one(A, J, smem, threadIdx.x);
+            return;
+        }
+    }
+    run_small<LW>(A, J, smem, threadIdx.x);
 }
 
 template <int L, bool COH>
@@ -222,7 +264,7 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void b
     uint32_t tk = __builtin_amdgcn_readfirstlane(s_ticket);
     for (;;) {
         if (tk >= end) break;
-        const BatchTask task = A.tasks[tk];
+        const BatchTask &task = A.tasks[tk];  // (read where used: held in registers it spilled)
         const BatchJob &J = task.J;
         // the next ticket is claimed now and read after the task, so the
         // atomic's round trip overlaps the work
@@ -235,12 +277,8 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void b
         switch (J.kind) {
         case kPassA: run_a<COH>(A, J, task.tile, smem, tid); break;
         case kPassB: run_b(A, J, task.tile, smem, tid); break;
-        case kOne: {
-            const TopRoots T = A.tabs[J.tab];
-            chip14_tile(A.in + J.base, A.out + J.base, A.stw + A.stw_off[13], T.hi, T.lo, smem, own(tid), false, 0.f);
-            break;
-        }
-        default: run_small(A, J, smem, tid); break;
+        case kOne: run_one(A, J, smem, tid); break;
+        default: run_small<kLogBT>(A, J, smem, tid); break;
         }
         // Completion: once every wave has seen its stores complete (vmcnt 0)
         // a relaxed device-scope increment publishes the tile (the ordering a
@@ -252,9 +290,13 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void b
         tk = __builtin_amdgcn_readfirstlane(s_ticket);
         __syncthreads();  // every wave has read s_ticket before thread 0 writes it again
     }
+    // Leaving: no order but "this workgroup's counter updates are performed
+    // before its exit is counted" is needed, so a wait and a relaxed add (an
+    // acquire-release add wrote back and dropped the XCD's L2 once per
+    // workgroup: with 512 of them 36.6 us for 512 transforms of 2^13).
     if (tid == 0) {
-        const uint32_t before = __hip_atomic_fetch_add(A.exits, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = before + 1 == gridDim.x;
+        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        s_last = __hip_atomic_fetch_add(A.exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
     }
     __syncthreads();
     if (s_last) {  // everyone else has left: rearm the counters for the next launch
@@ -267,9 +309,10 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void b
             if (got < len) atomicAdd(A.errors, len - got);
         }
         __syncthreads();  // every queue checked before its ticket is rearmed
-        for (uint32_t j = tid; j < A.njobs; j += kBT) A.done[j] = 0;
-        for (uint32_t j = tid; j < A.nq; j += kBT) A.tickets[j * kTicketStride] = 0;
-        if (tid == 0) *A.exits = 0;
+        const auto clear = [](uint32_t *c) { __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        for (uint32_t j = tid; j < A.njobs; j += kBT) clear(A.done + j);
+        for (uint32_t j = tid; j < A.nq; j += kBT) clear(A.tickets + j * kTicketStride);
+        if (tid == 0) clear(A.exits);
     }
 }
 
@@ -324,6 +367,7 @@ struct paco_batch_plan_s {
     int64_t gap = 0;
     int nq = 1;        // work queues
     bool coh = false;  // one queue served by several XCDs: coherent stores
+    int lw = 0;        // log2 threads of a plain launch (batch_small_kernel); 0: the persistent kernel
     paco_batch_options opt{};
     std::string desc;
 };
@@ -356,6 +400,22 @@ int resident_workgroups(bool coh)
     const hipError_t e = coh ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, paco::batch_kernel<true>, paco::kBT, 0)
                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, paco::batch_kernel<false>, paco::kBT, 0);
     if (e != hipSuccess) return 0;
+    return cus * std::max(per, 1);
+}
+
+const void *small_kernel_of(int lw)
+{
+    return lw == paco::kLogST ? reinterpret_cast<const void *>(paco::batch_small_kernel<paco::kLogST>)
+                              : reinterpret_cast<const void *>(paco::batch_small_kernel<paco::kLogBT>);
+}
+
+int resident_small(int lw)
+{
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, small_kernel_of(lw), 1 << lw, 0) != hipSuccess)
+        return 0;
     return cus * std::max(per, 1);
 }
 
@@ -423,13 +483,16 @@ paco_status build_batch(paco_batch_plan_s *P)
     // a transform then runs on one XCD alone: where the fullest queue would
     // hold more than 1.5 times its share (a few large transforms), all XCDs
     // serve one queue
+    P->lw = ks.back() <= kShortMaxLog2 ? kLogST : ks.back() <= kChipMaxLog2 ? kLogBT : 0;
+    const int lw = P->lw ? P->lw : kLogBT;
+    if (P->lw) nx = 1;
     if (deal(nx) * nx > P->total + P->total / 2 && nx > 1) {
         nx = 1;
         deal(nx);
     }
     P->coh = nx == 1 && nxcd != 1;  // several XCDs serve one queue
     P->nq = nx;
-    const int resident = resident_workgroups(P->coh);
+    const int resident = P->lw ? resident_small(P->lw) : resident_workgroups(P->coh);
     if (resident <= 0) return bfail(PACO_ERR_HIP, "occupancy query failed");
 
     // ---- jobs ---------------------------------------------------------------
@@ -456,7 +519,7 @@ paco_status build_batch(paco_batch_plan_s *P)
             J.dep = -1;
             J.ntiles = 1;
             if (k < kChipMaxLog2) {  // with the next transforms of its size
-                const int64_t most = std::max<int64_t>(1, std::min<int64_t>(share >> k, int64_t(1) << small_lt(k)));
+                const int64_t most = std::max<int64_t>(1, std::min<int64_t>(share >> k, int64_t(1) << small_lt(k, lw)));
                 J.kind = kSmall;
                 J.l1 = k;
                 J.base = int64_t(members.size());
@@ -493,9 +556,11 @@ paco_status build_batch(paco_batch_plan_s *P)
     }
 
     // ---- launch geometry -----------------------------------------------------
-    // per queue: a job's successor is emitted about `gap` tiles after it, a
-    // few times the workgroups that serve the queue
-    P->gap = 4 * int64_t(resident) / nx;
+    // per queue: a job's successor is emitted about `gap` tiles after it:
+    // twice the workgroups that serve the queue, so that it rarely waits and
+    // the intermediate is still near (batch of 4096 transforms 2^8..2^20 by
+    // the gap in workgroups per queue: 0.5 4.71 ms, 1 4.26, 2 3.77, 4 4.17)
+    P->gap = 2 * int64_t(resident) / nx;
     if (P->opt.flags & PACO_BATCH_SET_GAP) P->gap = P->opt.gap;
 
     // ---- task order, queue by queue ------------------------------------------
@@ -605,13 +670,17 @@ paco_status build_batch(paco_batch_plan_s *P)
     // at least one workgroup per queue: workgroups are dealt to the XCDs in
     // turn, so every XCD's queue has a server (the exit check of the kernel
     // counts any queue left unserved anyway)
-    P->grid = int(std::max<int64_t>(std::min<int64_t>(int64_t(resident), int64_t(tasks.size())), int64_t(nx)));
+    P->grid = P->lw ? int(jobs.size())
+                    : int(std::max<int64_t>(std::min<int64_t>(int64_t(resident), int64_t(tasks.size())), int64_t(nx)));
 
     char buf[256];
     std::snprintf(buf, sizeof buf,
                   "batch[%d transforms, %lld items, %zu jobs, %zu tasks, %d %s, grid %d x %d, lds %zu, gap %lld]",
                   count, (long long)P->total, jobs.size(), tasks.size(), nx,
-                  P->coh ? "shared queue (coherent stores)" : "queues (one per XCD)", P->grid, kBT, size_t(paco::batch_lds()) * 8,
+                  P->lw ? "task list (one workgroup per task)"
+                  : P->coh ? "shared queue (coherent stores)"
+                           : "queues (one per XCD)",
+                  P->grid, 1 << lw, size_t(paco::plain_lds(lw)) * 8,
                   (long long)P->gap);
     P->desc = buf;
     for (auto &kv : P->plans) {
@@ -632,6 +701,7 @@ hipError_t launch_batch(const paco_batch_plan_s *P, const void *in, void *out, v
     A.out = static_cast<float2 *>(out);
     A.ws = static_cast<float2 *>(ws);
     void *args[] = {&A};
+    if (P->lw) return hipLaunchKernel(small_kernel_of(P->lw), dim3(unsigned(P->grid)), dim3(1u << P->lw), args, 0, s);
     return hipLaunchKernel(kernel_of(P->coh), dim3(unsigned(P->grid)), dim3(paco::kBT), args, 0, s);
 }
 

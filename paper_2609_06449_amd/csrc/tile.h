@@ -207,7 +207,11 @@ __device__ __forceinline__ void chip14_tile(const float2 *src, float2 *dst, cons
 
 // ---- the two column passes -----------------------------------------------------
 
-// Pass A: columns col0 .. of x (M1 = 2^L rows of M2 = 2^l2 items).
+// Pass A: columns col0 .. of x (M1 = 2^L rows of M2 = 2^l2 items).  The wide
+// tiles (H = 2) read x and write y with non-temporal accesses: both are used
+// once, and the buffer between the passes then stays in the caches (batch of
+// 4096 transforms 2^8..2^20 3.80 -> 3.63 ms, 128 of 2^20 812 -> 778 us, that
+// is 5.5 TB/s over its two passes, a large copy's rate; 2^23 90 -> 80 us).
 template <int L, int LT, int H, bool COH>
 __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int l2, int lb, uint32_t col0,
                                             const float2 *stw, float2 *smem, int tid, bool conj_in)
@@ -220,7 +224,7 @@ __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int 
         for (int r = 0; r < R; ++r) {
             const float2 *p = off32(src, (uint32_t(j + (r << LJ)) << l2) + uint32_t(t * H));
             if constexpr (H == 2) {
-                const float4 a = *reinterpret_cast<const float4 *>(p);
+                const float4 a = ld4_last(p);
                 u[r] = make_float2(a.x, a.y);
                 u[E + r] = make_float2(a.z, a.w);
             } else {
@@ -305,7 +309,7 @@ __device__ __forceinline__ void pass_b_tile(const float2 *src, float2 *dst, int 
             const float2 y0 = oscale != 0.f ? conj_scale(u[r], oscale) : u[r];
             if constexpr (H == 2) {
                 const float2 y1 = oscale != 0.f ? conj_scale(u[E + r], oscale) : u[E + r];
-                *reinterpret_cast<float4 *>(p) = make_float4(y0.x, y0.y, y1.x, y1.y);
+                __builtin_nontemporal_store(nt_f4{y0.x, y0.y, y1.x, y1.y}, reinterpret_cast<nt_f4 *>(p));
             } else {
                 *p = y0;
             }
