@@ -671,29 +671,28 @@ paco_status create_with_inverse(paco_plan **plan, int64_t N1, int64_t N2, int64_
     paco_status st = create_impl(plan, N1, N2, p, b, dt, opt);
     if (st != PACO_OK || (*plan)->direct) return st;  // (the direct form's split of N is its own)
     const std::string note = g_last_error;
-    // FP32 from 2^24 items on: the balanced shape of N runs the symmetric
-    // form's three passes, which no other shape beats.  Shapes without that
-    // form take its passes, and so does the inverse of non-square ones (on one
-    // HBM every shape is a view of the same vector).  us before / after:
-    // 1024 x 16384 232 / 162, 2048 x 16384 470 / 322, 2048 x 32768 986 / 657;
-    // inverses 4096 x 16384 777 / 655, 8192 x 32768 5300 / 2960 (its 32768 x
-    // 8192 passes were five).  Plan options that ask for a form keep the
-    // shape's own passes.
-    const int lN = (*plan)->lN;
+    // FP32 from 2^24 items on: the shape of N whose three passes of the
+    // symmetric form are the fastest, the balanced one and 8192 x 32768 at
+    // 2^28.  Shapes without that form run its passes, 16384 x 16384 does, and
+    // so does the inverse of every other shape (on one HBM a shape is a view
+    // of the same vector; the stage hooks keep the shape's own passes).
+    // us before / after: 1024 x 16384 232 / 137, 2048 x 16384 470 / 290,
+    // 2048 x 32768 986 / 610, 16384 x 16384 2900 / 2707; inverses 4096 x 16384
+    // 777 / 610, 8192 x 32768 5300 / 2707 (its 32768 x 8192 passes were
+    // five).  Plan options that ask for a form keep the shape's own passes.
+    const int lN = (*plan)->lN, best1 = lN == 28 ? 13 : lN / 2;
     const bool plain = !(opt.flags & ~PACO_PLAN_MIXED) && !opt.groups1 && !opt.groups3 && !opt.cols_long;
-    paco_plan *best = nullptr;
-    if (dt == PACO_C64 && plain && lN >= 24 && !((*plan)->sym && N1 == N2)) {
+    if (dt == PACO_C64 && plain && lN >= 24) {
+        if ((*plan)->l1 == best1) return PACO_OK;  // the inverse runs its own passes
+        paco_plan *best = nullptr;
         paco_plan_options o{};
-        if (create_impl(&best, int64_t(1) << (lN / 2), int64_t(1) << (lN - lN / 2), 2, 2, dt, o) != PACO_OK) best = nullptr;
+        if (create_impl(&best, int64_t(1) << best1, int64_t(1) << (lN - best1), 2, 2, dt, o) != PACO_OK) best = nullptr;
         g_last_error = note;
-    }
-    if (best && !(*plan)->sym) {
-        (*plan)->fwd = best;  // the inverse runs it too
-        return PACO_OK;
-    }
-    if (best) {
-        (*plan)->inv = best;
-        return PACO_OK;
+        if (best) {
+            if (!(*plan)->sym || N1 == N2) (*plan)->fwd = best;  // and the inverse
+            else (*plan)->inv = best;
+            return PACO_OK;
+        }
     }
     if (N1 == N2) return st;  // square: the inverse reuses the forward passes
     paco_plan *inv = nullptr;

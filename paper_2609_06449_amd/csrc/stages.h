@@ -112,6 +112,13 @@ __device__ __forceinline__ float4 ld4_last(const float2 *p)
 // Store of an item.  COH: a device-coherent store (written through this
 // XCD's L2), for results another workgroup of the same launch reads after a
 // completion counter says they are there.
+__device__ __forceinline__ float2 ld2_nt(const float2 *p, bool nt) { return nt ? ld2_last(p) : *p; }  // nt: a constant
+__device__ __forceinline__ void st2_nt(float2 *p, float2 v, bool nt)
+{
+    if (nt) st2_stream(p, v);
+    else *p = v;
+}
+
 template <bool COH>
 __device__ __forceinline__ void st2(char *p, float2 v)
 {

@@ -64,8 +64,7 @@ __device__ __forceinline__ float2 root_of(const float2 *tw, int log2L, int log2M
 // w_256^{-jl kl}, radix 16 over jl by thread (kl, cl), k = kl + 16 kh, then
 // w_N1^{-k r} = w_N1^{-kl r} w_N1^{-16 kh r}.  Loads: four 128-byte row runs
 // per instruction; stores: four 128-byte runs of U (k fastest).  STREAM:
-// non-temporal stores (ws is read once, by pass 2: measured 10 us faster
-// over the first two passes than plain stores at 2^24).
+// non-temporal stores of ws (see SymTemporal below).
 template <bool STREAM>
 __global__ __launch_bounds__(kSymThreads) void sym_first_kernel(SymPass P)
 {
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_first_kernel(SymPass P)
     float2 v[16];
     const float2 *src = P.src + addr::sym1_load_base(N2, blk, tid);
 #pragma unroll
-    for (int jh = 0; jh < 16; ++jh) v[jh] = src[addr::sym1_load_off(N2, jh)];
+    for (int jh = 0; jh < 16; ++jh) v[jh] = ld2_last(src + addr::sym1_load_off(N2, jh));
     // every twiddle factor, issued behind the data loads
     float2 t256[16], b[16];
 #pragma unroll
@@ -104,11 +103,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_first_kernel(SymPass P)
 #pragma unroll
     for (int kh = 0; kh < 16; ++kh) {
         const float2 y = cmul(v[kh], cmul(a, b[kh]));
-        float2 *d = dst + addr::sym1_store_off(N2, kh);
-        if constexpr (STREAM)
-            st2_stream(d, y);
-        else
-            *d = y;
+        st2_nt(dst + addr::sym1_store_off(N2, kh), y, STREAM);
     }
 }
 
@@ -183,7 +178,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_last_kernel(SymPass P)
     const float2 *src = P.src + addr::sym3_load_base(N1, blk, tid);
     float2 v[16];
 #pragma unroll
-    for (int jh = 0; jh < 16; ++jh) v[jh] = src[addr::sym3_load_off(N1, jh)];
+    for (int jh = 0; jh < 16; ++jh) v[jh] = ld2_last(src + addr::sym3_load_off(N1, jh));
     float2 t256[16];
 #pragma unroll
     for (int k = 1; k < 16; ++k) t256[k] = root_of(P.tw, P.log2L, 8, uint32_t(jl * k));
@@ -200,7 +195,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_last_kernel(SymPass P)
     float2 *dst = P.dst + addr::sym3_store_base(N1, blk, tid);
 #pragma unroll
     for (int kh = 0; kh < 16; ++kh)
-        dst[addr::sym3_store_off(N1, kh)] = P.out_scale != 0.f ? conj_scale(v[kh], P.out_scale) : v[kh];
+        st2_stream(dst + addr::sym3_store_off(N1, kh), P.out_scale != 0.f ? conj_scale(v[kh], P.out_scale) : v[kh]);
 }
 
 // ---- passes 1 and 3 for L = 512 and 1024 (N1 = N2 = 8192, 16384) ----------
@@ -292,7 +287,7 @@ __global__ __launch_bounds__(1 << LL) __attribute__((amdgpu_waves_per_eu(4))) vo
     auto load = [&](uint32_t tile) {
         const uint32_t base = addr::sym1_load_base(N2, addr::sym1_block(tile, N2, LL), tid);
 #pragma unroll
-        for (int jh = 0; jh < 16; ++jh) v[jh] = *off32(P.src, base + addr::sym1_load_off(N2, jh, LL));
+        for (int jh = 0; jh < 16; ++jh) v[jh] = ld2_last(off32(P.src, base + addr::sym1_load_off(N2, jh, LL)));
     };
     // stage A of tile tc (radix 16 over jh by thread (cl, jl), twiddle
     // w_L^{-jl ka}) into the exchange buffer, then the next tile's loads
@@ -332,11 +327,7 @@ __global__ __launch_bounds__(1 << LL) __attribute__((amdgpu_waves_per_eu(4))) vo
         for (int i = 0; i < 16; ++i) {
             // w_N1^{-k r}, k = ka + 16 (i + 16 jp): w_N1^{-ka r} w_L^{-(i + 16 jp) r}
             const float2 y = cmul(u[i], cmul(a, twL[((i + 16 * jp) * r) & (L - 1)]));
-            float2 *d = off32(P.dst, dbase + addr::sym1_store_off(N2, i));
-            if constexpr (STREAM)
-                st2_stream(d, y);
-            else
-                *d = y;
+            st2_nt(off32(P.dst, dbase + addr::sym1_store_off(N2, i)), y, STREAM);
         }
         __syncthreads();
         t += gridDim.x;
@@ -350,7 +341,8 @@ __global__ __launch_bounds__(1 << LL) __attribute__((amdgpu_waves_per_eu(4))) vo
 // for the 128-byte runs of the rows it stores; a half-wave of stage-B loads
 // (16 cl x 2 jp) is 32 consecutive items of one plane, so the planes need no
 // padding.  R = 2^LR: the radix of pass 2's Phase III child (rows R t + q0).
-template <int LL, int LR>
+// NTL, NTS: non-temporal loads and stores.
+template <int LL, int LR, bool NTL, bool NTS>
 __global__ __launch_bounds__(1 << LL) __attribute__((amdgpu_waves_per_eu(4))) void sym_last_long_kernel(SymPass P,
                                                                                                        uint32_t tiles)
 {
@@ -364,7 +356,7 @@ __global__ __launch_bounds__(1 << LL) __attribute__((amdgpu_waves_per_eu(4))) vo
     auto load = [&](uint32_t tile) {
         const uint32_t base = addr::sym3r_load_base(N1, addr::sym3r_block(tile, N1, LL, LR), tid, LR);
 #pragma unroll
-        for (int jh = 0; jh < 16; ++jh) v[jh] = *off32(P.src, base + addr::sym3r_load_off(N1, jh, LL, LR));
+        for (int jh = 0; jh < 16; ++jh) v[jh] = ld2_nt(off32(P.src, base + addr::sym3r_load_off(N1, jh, LL, LR)), NTL);
     };
     auto stage_a = [&](uint32_t tc) {
         const uint32_t jl = opaque(uint32_t(tid)) >> 4;
@@ -393,8 +385,8 @@ __global__ __launch_bounds__(1 << LL) __attribute__((amdgpu_waves_per_eu(4))) vo
         const uint32_t dbase = addr::sym3r_store_base(N1, blk, tid, LL, LR);
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            *off32(P.dst, dbase + addr::sym3r_store_off(N1, i, LR)) =
-                P.out_scale != 0.f ? conj_scale(u[i], P.out_scale) : u[i];
+            st2_nt(off32(P.dst, dbase + addr::sym3r_store_off(N1, i, LR)),
+                   P.out_scale != 0.f ? conj_scale(u[i], P.out_scale) : u[i], NTS);
         __syncthreads();
         t += gridDim.x;
         if (t < tiles) stage_a(t);
@@ -481,6 +473,49 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void s
     }
 }
 
+// Which accesses are non-temporal.  x is read once and y written once, and
+// what is kept out of the 256 MiB MALL leaves room for the two buffers that
+// the next pass reads; but where those do not fit either, partial reuse
+// decides, so the choices were measured, all 16 of them on 10 shapes, with
+// inputs and outputs that no cache holds (three sets of buffers in turn):
+//   pass 1 reads x with last-use loads everywhere; it streams ws (of which
+//   the MALL then holds nothing for pass 2) above 2^26 items only;
+//   pass 3 reads W with last-use loads and streams y at L2 = 256 and in the
+//   wide form; the persistent radix-16 kernels stream y up to 2^26 items at
+//   L2 = 1024 and always at L2 = 512, and read last-use from 2^27 items on at
+//   L2 = 512, at 2^28 at L2 = 1024.
+// us per transform, against plain accesses but a streamed ws (which had been
+// tuned on one set of buffers, half of it in the MALL): 4096^2 162-166 ->
+// 137, 4096 x 8192 322 -> 280-297, 8192^2 660 -> 607-614, 4096 x 16384 731 ->
+// 704-709, 16384 x 4096 779 -> 689, 16384^2 2972 -> 2900-2920, 4096 x 32768
+// 1425 -> 1323, 8192 x 32768 2973 -> 2707; 8192 x 16384 and 16384 x 8192 within
+// 3% of 1387 and 1419.  One set of buffers over and over: 4096^2 136.5 -> 134.
+struct SymTemporal {
+    bool stream1, last3, stream3;
+    SymTemporal(const SymPass &p, int ll2, int lr2)
+        : stream1(p.log2N > 26), last3(lr2 == 5 || (ll2 == 9 ? p.log2N > 26 : p.log2N > 27)),
+          stream3(lr2 == 5 || ll2 == 9 || p.log2N <= 26) {}
+};
+
+// pass 3 at L2 >= 512
+typedef void (*SymLastLong)(SymPass, uint32_t);
+SymLastLong last_long(const SymPass &p, int ll2, int lr2)
+{
+    const SymTemporal t(p, ll2, lr2);
+    if (lr2 == 5) return sym_last_long_kernel<10, 5, true, true>;
+    if (ll2 == 9) return t.last3 ? sym_last_long_kernel<9, 4, true, true> : sym_last_long_kernel<9, 4, false, true>;
+    return t.last3     ? sym_last_long_kernel<10, 4, true, false>
+           : t.stream3 ? sym_last_long_kernel<10, 4, false, true>
+                       : sym_last_long_kernel<10, 4, false, false>;
+}
+// pass 1 at L1 >= 512
+SymLastLong first_long(const SymPass &p, int ll1)
+{
+    const bool st = SymTemporal(p, 0, 0).stream1;
+    if (ll1 == 9) return st ? sym_first_long_kernel<true, 9> : sym_first_long_kernel<false, 9>;
+    return st ? sym_first_long_kernel<true, 10> : sym_first_long_kernel<false, 10>;
+}
+
 bool sym_shape_ok(const SymPass &p, int &ll1, int &ll2, int &lr2)
 {
     return sym_children(p, ll1, ll2, lr2) && p.src && p.dst && p.tw && p.tw_hi && p.tw_lo && p.tw_sj;
@@ -523,19 +558,8 @@ uint32_t sym_resident_groups(int pass, const SymPass &p)
     if (!sym_children(p, ll1, ll2, lr2)) return 0;
     if (pass == 2)
         return lr2 != 5 ? 0 : ll1 == 8 ? resident(sym_middle_wide_kernel<8, 10>, 512) : resident(sym_middle_wide_kernel<9, 10>, 512);
-    if (pass == 1) {
-        switch (ll1) {
-        case 9: return resident(sym_first_long_kernel<true, 9>, 512);
-        case 10: return resident(sym_first_long_kernel<true, 10>, 1024);
-        default: return 0;
-        }
-    }
-    if (lr2 == 5) return resident(sym_last_long_kernel<10, 5>, 1024);
-    switch (ll2) {
-    case 9: return resident(sym_last_long_kernel<9, 4>, 512);
-    case 10: return resident(sym_last_long_kernel<10, 4>, 1024);
-    default: return 0;
-    }
+    if (pass == 1) return ll1 < 9 ? 0 : resident(first_long(p, ll1), 1 << ll1);
+    return ll2 < 9 ? 0 : resident(last_long(p, ll2, lr2), 1 << ll2);
 }
 
 hipError_t launch_sym_first(const SymPass &p, hipStream_t s)
@@ -543,11 +567,12 @@ hipError_t launch_sym_first(const SymPass &p, hipStream_t s)
     int ll1 = 0, ll2 = 0, lr2 = 0;
     if (!sym_shape_ok(p, ll1, ll2, lr2)) return hipErrorInvalidValue;
     const dim3 grid(addr::sym1_groups(uint32_t(p.N2)));
-    switch (ll1) {
-    case 8: hipLaunchKernelGGL(sym_first_kernel<true>, grid, dim3(kSymThreads), 0, s, p); break;
-    case 9: hipLaunchKernelGGL((sym_first_long_kernel<true, 9>), persistent(grid, p.resident1), dim3(512), 0, s, p, grid.x); break;
-    default: hipLaunchKernelGGL((sym_first_long_kernel<true, 10>), persistent(grid, p.resident1), dim3(1024), 0, s, p, grid.x); break;
-    }
+    if (ll1 >= 9)
+        hipLaunchKernelGGL(first_long(p, ll1), persistent(grid, p.resident1), dim3(1u << ll1), 0, s, p, grid.x);
+    else if (SymTemporal(p, ll2, lr2).stream1)
+        hipLaunchKernelGGL(sym_first_kernel<true>, grid, dim3(kSymThreads), 0, s, p);
+    else
+        hipLaunchKernelGGL(sym_first_kernel<false>, grid, dim3(kSymThreads), 0, s, p);
     return hipGetLastError();
 }
 
@@ -576,17 +601,11 @@ hipError_t launch_sym_last(const SymPass &p, hipStream_t s)
 {
     int ll1 = 0, ll2 = 0, lr2 = 0;
     if (!sym_shape_ok(p, ll1, ll2, lr2)) return hipErrorInvalidValue;
-    if (lr2 == 5) {
-        const dim3 grid(addr::sym3r_groups(uint32_t(p.N1), 5));
-        hipLaunchKernelGGL((sym_last_long_kernel<10, 5>), persistent(grid, p.resident3), dim3(1024), 0, s, p, grid.x);
-        return hipGetLastError();
-    }
-    const dim3 grid(addr::sym3_groups(uint32_t(p.N1)));
-    switch (ll2) {
-    case 8: hipLaunchKernelGGL(sym_last_kernel, grid, dim3(kSymThreads), 0, s, p); break;
-    case 9: hipLaunchKernelGGL((sym_last_long_kernel<9, 4>), persistent(grid, p.resident3), dim3(512), 0, s, p, grid.x); break;
-    default: hipLaunchKernelGGL((sym_last_long_kernel<10, 4>), persistent(grid, p.resident3), dim3(1024), 0, s, p, grid.x); break;
-    }
+    const dim3 grid(addr::sym3r_groups(uint32_t(p.N1), uint32_t(lr2)));  // = sym3_groups at radix 16
+    if (ll2 >= 9)
+        hipLaunchKernelGGL(last_long(p, ll2, lr2), persistent(grid, p.resident3), dim3(1u << ll2), 0, s, p, grid.x);
+    else
+        hipLaunchKernelGGL(sym_last_kernel, grid, dim3(kSymThreads), 0, s, p);
     return hipGetLastError();
 }
 

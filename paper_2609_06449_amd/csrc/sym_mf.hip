@@ -117,6 +117,13 @@ __device__ __forceinline__ void mf_load_ops(const float2 (&it)[4], float (&x)[8]
     }
 }
 
+// Non-temporal accesses (the reasons in sym.hip, SymTemporal): pass 1 reads
+// x with last-use loads; at L = 256 it stores ws plainly and pass 3 reads W
+// with last-use loads, at L = 512 it streams ws and pass 3 streams y.  us per
+// transform on buffers that no cache holds, against plain accesses but a
+// streamed ws, FP16x3 / BF16x3 / BF16x6: 4096^2 184 / 179 / 188 -> 169 / 161 /
+// 169 (one set of buffers over and over 152 / 149 / 159 -> 153 / 150 / 156),
+// 8192^2 717 / 697 / 726 -> 705 / 693 / 728.
 // Pass 1 (see sym.hip): stage 1 butterfly (cl = n, jl = 4 w + G) over jh,
 // stage 2 butterfly (kl = n, cl = 4 w + G) over jl.
 template <int PREC>
@@ -135,7 +142,7 @@ __global__ __launch_bounds__(256) void sym_first_mf_kernel(SymPass P)
         for (int G = 0; G < 4; ++G) {
             const float2 *src = P.src + addr::sym1_load_base(N2, blockIdx.x, uint32_t(n + 16 * (4 * w + G)));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) it[G][k] = src[addr::sym1_load_off(N2, uint32_t(8 * half + (comp ? 4 + k : k)))];
+            for (int k = 0; k < 4; ++k) it[G][k] = ld2_last(src + addr::sym1_load_off(N2, uint32_t(8 * half + (comp ? 4 + k : k))));
         }
 #pragma unroll
         for (int G = 0; G < 4; ++G) mf_load_ops(it[G], x[G], comp, P.conj_in != 0);
@@ -180,7 +187,7 @@ __global__ __launch_bounds__(256) void sym_first_mf_kernel(SymPass P)
 #pragma unroll
         for (int G = 0; G < 4; ++G) {
             float2 *d = P.dst + addr::sym1_store_base(N2, blockIdx.x, uint32_t(n + 16 * (4 * w + G)));
-            st2_stream(d + addr::sym1_store_off(N2, kh), cmul(o[G][i], t));
+            d[addr::sym1_store_off(N2, kh)] = cmul(o[G][i], t);
         }
     }
 }
@@ -286,7 +293,7 @@ __global__ __launch_bounds__(256) void sym_last_mf_kernel(SymPass P)
         for (int G = 0; G < 4; ++G) {
             const float2 *src = P.src + addr::sym3_load_base(N1, blockIdx.x, uint32_t(n + 16 * (4 * w + G)));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) it[G][q] = src[addr::sym3_load_off(N1, uint32_t(8 * half + (comp ? 4 + q : q)))];
+            for (int q = 0; q < 4; ++q) it[G][q] = ld2_last(src + addr::sym3_load_off(N1, uint32_t(8 * half + (comp ? 4 + q : q))));
         }
 #pragma unroll
         for (int G = 0; G < 4; ++G) mf_swap_in(it[G], x[G]);
@@ -388,7 +395,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PREC == kPr
             const uint32_t base = addr::sym1_load_base(N2, blk, uint32_t(n + 16 * (4 * w + G)));
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                it[G][k] = *off32(P.src, base + addr::sym1_load_off(N2, uint32_t(8 * half + (comp ? 4 + k : k)), LL));
+                it[G][k] = ld2_last(off32(P.src, base + addr::sym1_load_off(N2, uint32_t(8 * half + (comp ? 4 + k : k)), LL)));
         }
     };
     int e = 0;  // FP16x3: the tile's scale, from stage A to the stores
@@ -521,8 +528,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void s
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float2 y = o[kc][i];
-                    *off32(P.dst, d + addr::sym3_store_off(N1, uint32_t(4 * kb + i))) =
-                        P.out_scale != 0.f ? conj_scale(y, P.out_scale * osc) : make_float2(y.x * osc, y.y * osc);
+                    st2_stream(off32(P.dst, d + addr::sym3_store_off(N1, uint32_t(4 * kb + i))),
+                               P.out_scale != 0.f ? conj_scale(y, P.out_scale * osc)
+                                                  : make_float2(y.x * osc, y.y * osc));
                 }
             }
         }

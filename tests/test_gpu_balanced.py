@@ -21,6 +21,11 @@ def _call(fn, xd):
     return out
 
 
+def _best(k):
+    l1 = 13 if k == 28 else k // 2
+    return 1 << l1, 1 << (k - l1)
+
+
 def _dev(x):
     return torch.from_numpy(x).to("cuda")
 
@@ -33,7 +38,7 @@ def test_runs_the_balanced_passes(N1, N2, p, b, mixed):
     x = inputs.normal(N, seed=k + N1)
     xd = _dev(x)
     plan = paco.Plan(N1, N2, p, b, mixed=mixed)
-    best = paco.Plan(1 << (k // 2), 1 << (k - k // 2), 2, 2)
+    best = paco.Plan(*_best(k), 2, 2)
     assert plan.launches == 3 and "executes sym[" in plan.description and best.has_split == 2
     y = _call(plan.execute, xd)
     assert torch.equal(y, _call(best.execute, xd))
@@ -49,16 +54,29 @@ def test_runs_the_balanced_passes(N1, N2, p, b, mixed):
     assert oracle.rel_l2(_call(plan.execute, z).cpu().numpy(), x) <= 2 * TOL
 
 
-@pytest.mark.parametrize("N1,N2", [(4096, 1 << 13), (1 << 14, 4096), (4096, 1 << 15)])
+@pytest.mark.parametrize("N1,N2", [(1 << 13, 4096), (1 << 14, 4096), (4096, 1 << 15), (1 << 13, 1 << 14)])
 def test_inverse_of_non_square_symmetric_shapes(N1, N2):
     k = (N1 * N2).bit_length() - 1
     plan = paco.Plan(N1, N2, 64, 2)
-    best = paco.Plan(1 << (k // 2), 1 << (k - k // 2), 2, 2)
+    best = paco.Plan(*_best(k), 2, 2)
     x = inputs.normal(N1 * N2, seed=k)
     y = _call(plan.execute, _dev(x))
     back = _call(plan.execute_inverse, y)
     assert torch.equal(back, _call(best.execute_inverse, y))
     assert oracle.rel_l2(back.cpu().numpy(), x) <= 2 * TOL
+
+
+def test_2p28_square_and_wide_agree():
+    x = torch.view_as_complex(torch.randn(1 << 28, 2, device="cuda", generator=torch.Generator("cuda").manual_seed(3)))
+    square, wide = paco.Plan(1 << 14, 1 << 14, 256, 4), paco.Plan(1 << 13, 1 << 15, 128, 2)
+    assert square.has_split == 2 and "executes sym[" in square.description and "executes" not in wide.description
+    y = _call(square.execute, x)
+    assert torch.equal(y, _call(wide.execute, x))
+    back = _call(square.execute_inverse, y)
+    assert torch.equal(back, _call(wide.execute_inverse, y))
+    assert ((back - x).norm() / x.norm()).item() <= 2 * TOL
+    del y, back, x
+    torch.cuda.empty_cache()
 
 
 def test_stage_hooks_and_options_keep_the_shape():
