@@ -9,20 +9,10 @@
 // workgroup's kernel takes 4.7 us at 2^12, 6.7 at 2^13 and 12.2 at 2^14,
 // where two passes of 3.8 and 4.3 us would be as fast back to back but pay
 // the second launch when a call is waited for.
-#include "tile.h"
+#include "direct_kernels.h"
 
 namespace paco {
 namespace {
-
-struct DirectArgs {
-    const float2 *src;
-    float2 *dst;
-    const float2 *stw;
-    TopRoots top;
-    int32_t l1, l2;
-    int32_t conj_in;
-    float out_scale;
-};
 
 template <int L>
 __global__ __launch_bounds__(tile_threads(L, 0, 1)) void direct_chip_kernel(DirectArgs P)
@@ -35,58 +25,6 @@ __global__ __launch_bounds__(512) void direct_chip14_kernel(DirectArgs P)
 {
     __shared__ float2 smem[tile_lds(13, 1, 2)];
     chip14_tile(P.src, P.dst, P.stw, P.top.hi, P.top.lo, smem, threadIdx.x, P.conj_in != 0, P.out_scale);
-}
-
-// Tiles of 4 columns: 32-byte runs of x and of y, which the tiles beside it on
-// the same XCD (tile_order) complete to lines in its L2.  What bounds a pass
-// here is its launch and one chain of load, arithmetic, store per workgroup,
-// so the most workgroups win: 4 columns against 8 in both passes took 11.2
-// against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
-// 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
-constexpr int kLT = 2;
-// 4096-point columns (2^23 only): two LDS groups of two columns, 64 KiB, so
-// two workgroups share a CU.  2^23: 90 us; the three-pass forms it replaces
-// took 95 to 130 by shape.  2^24 in two passes took 191 us against 162 for the
-// symmetric form's three, which ends the range.
-constexpr int groups(int l) { return l == 12 ? 2 : 1; }
-
-template <int L>
-__global__ __launch_bounds__(tile_threads(L, kLT, groups(L))) void direct_a_kernel(DirectArgs P)
-{
-    __shared__ float2 smem[tile_lds(L, kLT, groups(L))];
-    pass_a_tile<L, kLT, groups(L), false>(P.src, P.dst, P.l2, kLT, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.stw,
-                                  smem, threadIdx.x, P.conj_in != 0);
-}
-
-template <int L>
-__global__ __launch_bounds__(tile_threads(L, kLT, groups(L))) void direct_b_kernel(DirectArgs P)
-{
-    __shared__ float2 smem[tile_lds(L, kLT, groups(L))];
-    pass_b_tile<L, kLT, groups(L)>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << kLT, P.top, P.stw, smem,
-                           threadIdx.x, P.out_scale);
-}
-
-template <int L>
-void launch_pass(bool b, unsigned tiles, const DirectArgs &a, hipStream_t s)
-{
-    if (b) hipLaunchKernelGGL(direct_b_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, groups(L))), 0, s, a);
-    else hipLaunchKernelGGL(direct_a_kernel<L>, dim3(tiles), dim3(tile_threads(L, kLT, groups(L))), 0, s, a);
-}
-
-// one pass of 2^l points over 2^lcols columns
-hipError_t pass(bool b, int l, int lcols, const DirectArgs &a, hipStream_t s)
-{
-    const unsigned tiles = 1u << (lcols - kLT);
-    switch (l) {
-    case 7: launch_pass<7>(b, tiles, a, s); break;
-    case 8: launch_pass<8>(b, tiles, a, s); break;
-    case 9: launch_pass<9>(b, tiles, a, s); break;
-    case 10: launch_pass<10>(b, tiles, a, s); break;
-    case 11: launch_pass<11>(b, tiles, a, s); break;
-    case 12: launch_pass<12>(b, tiles, a, s); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
 }
 
 template <int L>
@@ -117,7 +55,7 @@ hipError_t launch_direct(const DirectForm &f, const float2 *in, float2 *out, flo
     a.src = in;
     a.stw = f.stw1;
     a.conj_in = inverse ? 1 : 0;
-    if (f.log2N <= kDirectChipLog2) {
+    if (f.l1 == 0) {
         a.dst = out;
         a.out_scale = scale;
         switch (f.log2N) {
@@ -139,14 +77,17 @@ hipError_t launch_direct(const DirectForm &f, const float2 *in, float2 *out, flo
         return hipGetLastError();
     }
     a.dst = ws;
-    hipError_t e = pass(false, f.l1, f.l2, a, s);
+    const auto pass = [&](bool b, int l, int lcols) {
+        return f.prec == kPrecFP32 ? direct_pass_t<kPrecFP32>(b, l, lcols, a, s) : direct_pass_mf(f.prec, b, l, lcols, a, s);
+    };
+    hipError_t e = pass(false, f.l1, f.l2);
     if (e != hipSuccess) return e;
     a.src = ws;
     a.dst = out;
     a.stw = f.stw2;
     a.conj_in = 0;
     a.out_scale = scale;
-    return pass(true, f.l2, f.l1, a, s);
+    return pass(true, f.l2, f.l1);
 }
 
 }  // namespace paco

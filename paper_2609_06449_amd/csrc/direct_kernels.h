@@ -1,0 +1,90 @@
+// The two column passes of the direct form (direct.hip), templated on the
+// butterfly arithmetic (direct_mf.hip instantiates the split MFMA forms).
+#pragma once
+
+#include "tile.h"
+
+namespace paco {
+
+struct DirectArgs {
+    const float2 *src;
+    float2 *dst;
+    const float2 *stw;
+    TopRoots top;
+    int32_t l1, l2;
+    int32_t conj_in;
+    float out_scale;
+};
+
+// the split MFMA forms' passes (direct_mf.hip)
+hipError_t direct_pass_mf(int prec, bool b, int l, int lcols, const DirectArgs &a, hipStream_t s);
+
+namespace {
+
+// Tiles of 4 columns: 32-byte runs of x and of y, which the tiles beside it on
+// the same XCD (tile_order) complete to lines in its L2.  What bounds a pass
+// here is its launch and one chain of load, arithmetic, store per workgroup,
+// so the most workgroups win: 4 columns against 8 in both passes took 11.2
+// against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
+// 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
+constexpr int kLT = 2;
+// 4096-point columns (2^23 only): two LDS groups of two columns, 64 KiB, so
+// two workgroups share a CU.  2^23: 90 us; the three-pass forms it replaces
+// took 95 to 130 by shape.  2^24 in two passes took 191 us against 162 for the
+// symmetric form's three, which ends the range.
+constexpr int groups(int l) { return l == 12 ? 2 : 1; }
+// (the split MFMA forms' butterflies need full waves: 8 columns of 128 points)
+__host__ __device__ constexpr int tile_cols(int l, int prec) { return prec != kPrecFP32 && l == 7 ? 3 : kLT; }
+
+template <int L, int PREC>
+__global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC), groups(L))) void direct_a_kernel(DirectArgs P)
+{
+    constexpr int LT = tile_cols(L, PREC);
+    __shared__ float2 smem[tile_lds(L, LT, groups(L))];
+    pass_a_tile<L, LT, groups(L), false, PREC>(P.src, P.dst, P.l2, tile_cols(P.l2, PREC),
+                                               uint32_t(tile_order(blockIdx.x, gridDim.x)) << LT, P.stw, smem,
+                                               threadIdx.x, P.conj_in != 0);
+}
+
+template <int L, int PREC>
+__global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC), groups(L))) void direct_b_kernel(DirectArgs P)
+{
+    constexpr int LT = tile_cols(L, PREC);
+    __shared__ float2 smem[tile_lds(L, LT, groups(L))];
+    pass_b_tile<L, LT, groups(L), PREC>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << LT, P.top,
+                                        P.stw, smem, threadIdx.x, P.out_scale);
+}
+
+template <int L, int PREC>
+void launch_pass(bool b, int lcols, const DirectArgs &a, hipStream_t s)
+{
+    constexpr int LT = tile_cols(L, PREC);
+    const dim3 tiles(1u << (lcols - LT)), threads(tile_threads(L, LT, groups(L)));
+    if (b) hipLaunchKernelGGL((direct_b_kernel<L, PREC>), tiles, threads, 0, s, a);
+    else hipLaunchKernelGGL((direct_a_kernel<L, PREC>), tiles, threads, 0, s, a);
+}
+
+// one pass of 2^l points over 2^lcols columns
+template <int PREC>
+hipError_t direct_pass_t(bool b, int l, int lcols, const DirectArgs &a, hipStream_t s)
+{
+    switch (l) {
+    case 7: launch_pass<7, PREC>(b, lcols, a, s); break;
+    case 8: launch_pass<8, PREC>(b, lcols, a, s); break;
+    case 9: launch_pass<9, PREC>(b, lcols, a, s); break;
+    case 10: launch_pass<10, PREC>(b, lcols, a, s); break;
+    case 11: launch_pass<11, PREC>(b, lcols, a, s); break;
+    case 12:
+        // split butterflies at 4096 points spilled and took 209 us at 2048 x 4096, the three-pass form 175
+        if constexpr (PREC == kPrecFP32) {
+            launch_pass<12, PREC>(b, lcols, a, s);
+            break;
+        }
+        return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace paco

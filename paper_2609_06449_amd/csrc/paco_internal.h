@@ -209,11 +209,13 @@ struct SymPass {
 // The direct form (direct.hip), FP32, N <= 2^23: one launch of one workgroup
 // up to 2^14 items, else two column passes over N = 2^l1 2^l2 (tile.h).  The
 // split of N is the library's own: neither N1 x N2 nor b nor p of the plan
-// enters the result.
+// enters the result.  The split MFMA forms run the two passes too, of the
+// lengths N1 and N2 of the plan (2^7 .. 2^11 each).
 constexpr int kDirectChipLog2 = 14;  // the largest transform of one workgroup
 constexpr int kDirectMaxLog2 = 23;
 struct DirectForm {
-    int32_t log2N, l1, l2;           // two passes: pass A 2^l1 points over 2^l2 columns, pass B the reverse
+    int32_t log2N, l1, l2;           // two passes: pass A 2^l1 points over 2^l2 columns, pass B the reverse (else 0)
+    int32_t prec;                    // radix-16 butterflies of the two passes (paco_dtype)
     const float2 *stw1, *stw2;       // stage tables of the two lengths (one workgroup: stw1)
     const float2 *hi, *lo;           // two-level table of w_N (split at 2^log2Lo)
     int32_t log2Lo;
@@ -259,7 +261,7 @@ hipError_t launch_middle(const MiddlePass &p, hipStream_t s);
 // The direct form's split of N = 2^log2N (tables unset).
 DirectForm direct_form(int log2N);
 // Kernel launches of the form.
-constexpr int direct_launches(int log2N) { return log2N <= kDirectChipLog2 ? 1 : 2; }
+inline int direct_launches(const DirectForm &f) { return f.l1 == 0 ? 1 : 2; }
 // The whole transform on stream s: in -> ws -> out (one workgroup: in -> out).
 // inverse: conj on load, conj times 1/N on store.
 hipError_t launch_direct(const DirectForm &f, const float2 *in, float2 *out, float2 *ws, bool inverse, hipStream_t s);

@@ -296,10 +296,22 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
     const bool fp32 = dt == PACO_C64 || (P->l1 < 4 && P->l2 < 4);
     P->direct = fp32 && plain && !(split_shape && P->lN <= 20) &&
                 P->lN <= paco::kDirectMaxLog2;
+    // the split MFMA forms: the phases' own lengths, so that the same
+    // butterflies run split and the errors stay what they were; sides of 2^7
+    // (a full wave of butterflies per tile) to 2^11 points (see direct_kernels.h)
+    const bool direct_mf = !fp32 && plain && P->l1 >= 7 && P->l1 <= 11 && P->l2 >= 7 && P->l2 <= 11;
     std::vector<float2> tdw;
-    if (P->direct) {
-        P->direct_form = paco::direct_form(P->lN);
-        if (P->lN > paco::kDirectChipLog2) {
+    if (P->direct || direct_mf) {
+        P->direct = true;
+        if (direct_mf) {
+            P->direct_form.log2N = P->lN;
+            P->direct_form.l1 = P->l1;
+            P->direct_form.l2 = P->l2;
+            P->direct_form.prec = int32_t(dt);
+        } else {
+            P->direct_form = paco::direct_form(P->lN);
+        }
+        if (P->direct_form.l1) {
             const int64_t n = int64_t(16) << P->direct_form.l1;
             tdw.resize(size_t(n));
             for (int64_t k = 0; k < n; ++k) tdw[k] = paco::root_neg(k, n);
@@ -345,7 +357,7 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
 
     if (P->direct) {
         paco::DirectForm &f = P->direct_form;
-        f.stw1 = d_stw + stw_off[P->lN <= paco::kDirectChipLog2 ? std::min(P->lN, paco::kStageMaxLog2) : f.l1];
+        f.stw1 = d_stw + stw_off[f.l1 == 0 ? std::min(P->lN, paco::kStageMaxLog2) : f.l1];
         f.stw2 = d_stw + stw_off[f.l2];
         f.hi = d_thi;
         f.lo = d_tlo;
@@ -627,7 +639,7 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
         desc += buf;
     }
     if (P->direct) {
-        if (P->lN <= paco::kDirectChipLog2)
+        if (P->direct_form.l1 == 0)
             std::snprintf(buf, sizeof buf, " direct[one workgroup, 2^%d points]", P->lN);
         else
             std::snprintf(buf, sizeof buf, " direct[two column passes, 2^%d x 2^%d]", P->direct_form.l1,
@@ -746,7 +758,7 @@ paco_status paco_plan_describe(const paco_plan *plan, int32_t *launches, char *b
     if (!plan) return fail(PACO_ERR_INVALID_ARG, "plan is NULL");
     if (launches)  // the split form runs its two passes in place of Phase I's passes and Phase II
         *launches = plan->fwd      ? 3
-                    : plan->direct ? paco::direct_launches(plan->lN)
+                    : plan->direct ? paco::direct_launches(plan->direct_form)
                     : plan->sym    ? 3
                                    : int32_t((plan->split ? 2 : plan->phase1.size() + 1) + plan->phase3.size());
     if (buf && buflen) {

@@ -70,12 +70,16 @@ __device__ __forceinline__ int tile_idx(int g)
 // called once per butterfly of the last stage with its R outputs
 // k = j + r 2^LNS at u[r] (group h: u[h E + r]).  The exchange buffer may be
 // written from the call on; slower threads may still read it after the return.
-template <int L, int S, int LTG, int H, bool JF, typename Store>
+// PREC: the radix-16 butterflies' arithmetic; the split MFMA forms use the
+// exchange buffer as the waves' scratch (full waves only).
+template <int L, int S, int LTG, int H, bool JF, int PREC = kPrecFP32, typename Store>
 __device__ __forceinline__ void tile_stage(float2 (&v)[H * tile_items(L)], float2 *lds, const float2 *twl, int tid,
                                            const Store &store)
 {
     constexpr int E = tile_items(L), LR = stage_log2radix(L, S), R = 1 << LR, LNS = stage_log2ns(L, S), NB = E / R;
     constexpr int NT = (1 << (L + LTG)) / E, LJ = L - LR;
+    constexpr bool MF = PREC != kPrecFP32 && LR == 4;
+    static_assert(!MF || (NT % 64 == 0 && NB == 1), "MFMA butterflies run on full waves");
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         if constexpr (LNS > 0) {
@@ -91,14 +95,21 @@ __device__ __forceinline__ void tile_stage(float2 (&v)[H * tile_items(L)], float
                 for (int h = 0; h < H; ++h) v[h * E + i * R + r] = cmul(v[h * E + i * R + r], w);
             }
         }
+        if constexpr (!MF) {
 #pragma unroll
-        for (int h = 0; h < H; ++h) dft_regs<LR>(&v[h * E + i * R]);
+            for (int h = 0; h < H; ++h) dft_regs<LR>(&v[h * E + i * R]);
+        }
+    }
+    if constexpr (MF) {
+        if constexpr (S > 0) __syncthreads();  // every wave has read its operands out of the buffer
+#pragma unroll
+        for (int h = 0; h < H; ++h) mfma_dft16<PREC>(&v[h * E], lds + ((tid >> 6) << 10), tid & 63);
     }
     if constexpr (S + 1 < stage_count(L)) {
         constexpr int LR2 = stage_log2radix(L, S + 1), R2 = 1 << LR2, NB2 = E / R2, LNR2 = L - LR2;
 #pragma unroll
         for (int h = 0; h < H; ++h) {
-            if (S > 0 || h > 0) __syncthreads();  // the previous contents were consumed
+            if (S > 0 || h > 0 || MF) __syncthreads();  // the previous contents were consumed
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 const int g = tid + i * NT;
@@ -116,7 +127,7 @@ __device__ __forceinline__ void tile_stage(float2 (&v)[H * tile_items(L)], float
                 for (int r = 0; r < R2; ++r) v[h * E + i * R2 + r] = lds[tile_slot<L, LTG, JF>(j + (r << LNR2), t)];
             }
         }
-        tile_stage<L, S + 1, LTG, H, JF>(v, lds, twl, tid, store);
+        tile_stage<L, S + 1, LTG, H, JF, PREC>(v, lds, twl, tid, store);
     } else {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -212,7 +223,7 @@ __device__ __forceinline__ void chip14_tile(const float2 *src, float2 *dst, cons
 // once, and the buffer between the passes then stays in the caches (batch of
 // 4096 transforms 2^8..2^20 3.80 -> 3.63 ms, 128 of 2^20 812 -> 778 us, that
 // is 5.5 TB/s over its two passes, a large copy's rate; 2^23 90 -> 80 us).
-template <int L, int LT, int H, bool COH>
+template <int L, int LT, int H, bool COH, int PREC = kPrecFP32>
 __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int l2, int lb, uint32_t col0,
                                             const float2 *stw, float2 *smem, int tid, bool conj_in)
 {
@@ -235,7 +246,7 @@ __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int 
     copy_twiddles(smem, stw, stage_tw_total(L), tid, tile_threads(L, LT, H));
     if (conj_in) tile_conj(v);
     const uint32_t lbm = (1u << lb) - 1u;
-    tile_stage<L, 0, LTG, H, false>(v, smem + tile_tw(L), smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
+    tile_stage<L, 0, LTG, H, false, PREC>(v, smem + tile_tw(L), smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t k = uint32_t(j + (r << LNS));
@@ -256,7 +267,7 @@ struct TopRoots {
     const float2 *hi, *lo, *cw;  // w_N^{-e} = hi[e >> log2Lo] lo[e mod 2^log2Lo]; cw[k] = w_{16 M1}^{-k}, k < 16 M1
     int log2N, log2Lo;
 };
-template <int L, int LT, int H>
+template <int L, int LT, int H, int PREC = kPrecFP32>
 __device__ __forceinline__ void pass_b_tile(const float2 *src, float2 *dst, int l1, uint32_t col0, const TopRoots &T,
                                             const float2 *stw, float2 *smem, int tid, float oscale)
 {
@@ -302,7 +313,7 @@ __device__ __forceinline__ void pass_b_tile(const float2 *src, float2 *dst, int 
         for (int h = 0; h < H; ++h) v[h * E + r] = cmul(v[h * E + r], cmul(a[h], cwt[(r << LT) + t0 + h]));
     __syncthreads();  // the factors are read: the exchange buffer is free
     dst += col0;
-    tile_stage<L, 0, LTG, H, false>(v, cwt, smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
+    tile_stage<L, 0, LTG, H, false, PREC>(v, cwt, smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             float2 *p = off32(dst, (uint32_t(j + (r << LNS)) << l1) + uint32_t(t * H));

@@ -146,3 +146,25 @@ def test_torch_calls_run_on_the_current_stream():
             out = ta.fft(y, 128, 64, 4, 2)
         torch.cuda.synchronize()
         assert oracle.rel_l2(out.cpu().numpy(), oracle.dft(x.cpu().numpy())) <= TOL
+
+
+@pytest.mark.parametrize("dt,tol", [(paco.PACO_C64_MFMA_FP16X3, 1e-6), (paco.PACO_C64_MFMA_BF16X3, 3e-5),
+                                    (paco.PACO_C64_MFMA_BF16X6, 1e-6)])
+@pytest.mark.parametrize("N1,N2,p,b,mixed", [(128, 128, 4, 2, False), (128, 2048, 8, 2, False), (2048, 128, 4, 16, True),
+                                             (512, 512, 16, 8, False), (1024, 256, 8, 4, False), (2048, 2048, 64, 4, True)])
+def test_split_forms_in_two_passes(N1, N2, p, b, mixed, dt, tol):
+    # the bounds of the split forms' other plans, on wide-range inputs
+    x = inputs.loguniform(N1 * N2, seed=N1 + 3 * N2)
+    plan = paco.Plan(N1, N2, p, b, dt, mixed=mixed)
+    assert plan.launches == 2 and " direct[" in plan.description, plan.description
+    xd = _dev(x)
+    y = _call(plan.execute, xd)
+    assert oracle.rel_l2(y, oracle.dft(x.astype(np.complex128))) <= tol
+    assert oracle.rel_l2(_call(plan.execute_inverse, xd), oracle.idft(x)) <= tol
+    buf = xd.clone()
+    assert np.array_equal(_bits(_call(plan.execute, buf, out=buf)), _bits(y))
+
+
+@pytest.mark.parametrize("N1,N2", [(64, 2048), (4096, 128), (128, 4096)])
+def test_split_forms_outside_the_two_passes_sides(N1, N2):
+    assert " direct[" not in paco.Plan(N1, N2, 4, 2, paco.PACO_C64_MFMA_BF16X6).description
