@@ -21,10 +21,10 @@ __global__ __launch_bounds__(tile_threads(L, 0, 1)) void direct_chip_kernel(Dire
     chip_tile<L, 0>(P.src, P.dst, [](int) { return int64_t(0); }, P.stw, smem, threadIdx.x, P.conj_in != 0, P.out_scale);
 }
 
-__global__ __launch_bounds__(512) void direct_chip14_kernel(DirectArgs P)
+__global__ __launch_bounds__(1024) void direct_chip14_kernel(DirectArgs P)
 {
-    __shared__ float2 smem[tile_lds(13, 1, 2)];
-    chip14_tile(P.src, P.dst, P.stw, P.top.hi, P.top.lo, smem, threadIdx.x, P.conj_in != 0, P.out_scale);
+    __shared__ float2 smem[tile_lds(13, 1, 1)];
+    chip14_wide_tile(P.src, P.dst, P.stw, P.top.hi, P.top.lo, smem, threadIdx.x, P.conj_in != 0, P.out_scale);
 }
 
 template <int L>
@@ -71,7 +71,7 @@ hipError_t launch_direct(const DirectForm &f, const float2 *in, float2 *out, flo
         case 11: chip<11>(a, s); break;
         case 12: chip<12>(a, s); break;
         case 13: chip<13>(a, s); break;
-        case 14: hipLaunchKernelGGL(direct_chip14_kernel, dim3(1), dim3(512), 0, s, a); break;
+        case 14: hipLaunchKernelGGL(direct_chip14_kernel, dim3(1), dim3(1024), 0, s, a); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();

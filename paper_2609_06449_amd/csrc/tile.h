@@ -216,6 +216,41 @@ __device__ __forceinline__ void chip14_tile(const float2 *src, float2 *dst, cons
     });
 }
 
+// The same by 1024 threads, for one transform alone: the groups are two
+// columns, and a thread's last-stage butterflies of column 1 are those of
+// column 0 with the same j, so the radix-2 step stays in registers.  The same
+// operations on every item as above.
+__device__ __forceinline__ void chip14_wide_tile(const float2 *src, float2 *dst, const float2 *stw,
+                                                 const float2 *__restrict__ hi, const float2 *__restrict__ lo,
+                                                 float2 *smem, int tid, bool conj_in, float oscale)
+{
+    constexpr int L = 13;
+    __builtin_assume(tid >= 0 && tid < 1024);
+    float2 v[16];
+    tile_load<L, 1, 1, true>(v, tid, [&](int t, int j, float2 *u, auto R, auto LJ) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[r] = src[2 * (j + (r << LJ)) + t];
+    });
+    copy_twiddles(smem, stw, stage_tw_total(L), tid, 1024);
+    if (conj_in) tile_conj(v);
+    float2 even[8];
+    tile_stage<L, 0, 1, 1, true>(v, smem + tile_tw(L), smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
+        static_assert(R == 2 && LNS == 12, "the last stage of 2^13 points");
+        const int i = (j >> 10) & 3;  // j = tid + 1024 i
+        if (t == 0) {
+            even[2 * i] = u[0];
+            even[2 * i + 1] = u[1];
+            return;
+        }
+        const float2 w = cmul(cmul(hi[(j & 511) >> 7], lo[j & 127]), hi[4 * (j >> 9)]);
+        const float2 o0 = cmul(u[0], w), o1 = cmul(u[1], w);
+        const float2 y[4] = {cadd(even[2 * i], o0), cadd(even[2 * i + 1], make_float2(o1.y, -o1.x)),
+                             csub(even[2 * i], o0), csub(even[2 * i + 1], make_float2(o1.y, -o1.x))};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dst[j + 4096 * q] = oscale != 0.f ? conj_scale(y[q], oscale) : y[q];
+    });
+}
+
 // ---- the two column passes -----------------------------------------------------
 
 // Pass A: columns col0 .. of x (M1 = 2^L rows of M2 = 2^l2 items).  The wide
