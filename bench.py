@@ -112,7 +112,7 @@ def kernel_hash() -> str:
 
 TRAFFIC_PATH = os.path.join(ROOT, "profiles", "traffic_2p24_4096x4096.json")
 # the passes of the default plan of the 2^24 workload, as rocprofv3 names their kernels
-SYM_KERNELS = ["pass1 sym_first_kernel<true>", "pass2 sym_middle_kernel<8,8>", "pass3 sym_last_kernel"]
+SYM_KERNELS = ["pass1 sym_first_kernel<false>", "pass2 sym_middle_kernel<8,8>", "pass3 sym_last_kernel"]
 COPY_BYTES = 1 << 28  # the --calibrate-copy device-to-device copy
 
 
@@ -285,11 +285,12 @@ def bench_batched(steps: int, warmup: int):
                         f"{E} items in total, one persistent launch replayed from a graph",
                gflops=round(flops / (ms * 1e-3) / 1e9, 1), ms_per_step=round(ms, 4),
                hbm_frac_3pass=round(48.0 * E / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+               hbm_frac_2pass=round(32.0 * E / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),  # the passes a large one makes
                loop_single_calls_ms=round(loop_ms, 3), loop_single_calls_graph_ms=round(loop_graph_ms, 3),
                speedup_vs_loop=round(loop_ms / ms, 2), speedup_vs_loop_graph=round(loop_graph_ms / ms, 2),
                plan_create_s=round(tune_s, 2), wait_timeouts=errors, plan=plan.description)
     if errors:  # a wait gave up: the launch completed with unspecified results
-        rec.update(valid=False, gflops=None, hbm_frac_3pass=None,
+        rec.update(valid=False, gflops=None, hbm_frac_3pass=None, hbm_frac_2pass=None,
                    note=f"{errors} completion waits hit their poll limit: results unspecified, not a measurement")
     del g, g2, x, out, ws
     for pl in singles.values():

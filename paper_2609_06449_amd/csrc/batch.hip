@@ -1,13 +1,14 @@
-// Batched form: many independent transforms of power-of-two sizes, each run
-// through the three phases of the paper (LocalFFT in output layout, the fused
-// global permutation with the top-level twiddle, LocalFFT in input layout),
-// all inside ONE persistent kernel launch.
+// Batched form: many independent transforms of power-of-two sizes, all inside
+// ONE kernel launch: in one workgroup up to 2^14 items, in two column passes
+// above (tile.h; the single plans' direct form, whose bits it gives).
 //
 // Work is cut into tasks: up to 2^13 items of whole transforms of one size
 // of at most 2^13 items, a whole transform of 2^14 items, or, for larger
 // ones, one 2^14-item tile of the first or of the second column pass of one
-// transform (tile.h; "jobs" are the (transform, pass) pairs).  A resident
-// workgroup claims the next task number from an atomic ticket counter.  A
+// transform ("jobs" are the (transform, pass) pairs).  A batch of the first
+// two kinds alone is a plain launch of one workgroup per task.  Otherwise the
+// launch is persistent: a resident workgroup claims the next task number from
+// an atomic ticket counter.  A
 // pass-B task waits until every tile of its transform's pass A is done, on a
 // per-job completion counter: the producer writes those tiles, waits for the
 // stores to complete and then increments the counter; the consumer reads the

@@ -29,9 +29,9 @@ namespace {
 // 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
 constexpr int kLT = 2;
 // 4096-point columns (2^23 only): two LDS groups of two columns, 64 KiB, so
-// two workgroups share a CU.  2^23: 90 us; the three-pass forms it replaces
-// took 95 to 130 by shape.  2^24 in two passes took 191 us against 162 for the
-// symmetric form's three, which ends the range.
+// two workgroups share a CU.  2^23: 80 us; the three-pass forms it replaces
+// took 95 to 130 by shape.  2^24 in two passes took 191 us against 162 (now
+// 132) for the symmetric form's three, which ends the range.
 constexpr int groups(int l) { return l == 12 ? 2 : 1; }
 // (the split MFMA forms' butterflies need full waves: 8 columns of 128 points)
 __host__ __device__ constexpr int tile_cols(int l, int prec) { return prec != kPrecFP32 && l == 7 ? 3 : kLT; }

@@ -75,12 +75,12 @@ __device__ __forceinline__ void dft_regs(float2 *v)
     for (int k = 0; k < R; ++k) v[k] = t[k];
 }
 
-// A streaming (non-temporal) 8-byte store, for a buffer whose one reader
-// streams it back in long contiguous runs (the packed Phase-I buffer and the
-// split form's buffer, read by the redistribution pass): HBM serves such
-// reads at copy speed, and keeping these lines out of the 256 MiB MALL
-// leaves room there for the input of the next transform and for Phase III's
-// input.
+// A streaming (non-temporal) 8-byte store: the line does not take up room in
+// the 256 MiB MALL.  For results that nothing reads again, and for a buffer
+// whose one reader streams it back in long contiguous runs (the packed
+// Phase-I buffer and the split form's, read by the redistribution pass), which
+// HBM serves at copy speed.  Only whole lines: on 32-byte runs it cost the
+// direct form 2^22 34 -> 59 us.
 __device__ __forceinline__ void st2_stream(void *p, float2 v)
 {
     typedef float sf2 __attribute__((ext_vector_type(2)));
@@ -90,12 +90,13 @@ __device__ __forceinline__ void st2_stream(void *p, float2 v)
     __builtin_nontemporal_store(t, reinterpret_cast<sf2 *>(p));
 }
 
-// Loads of data the transform never reads again (Phase II's source buffer):
-// non-temporal, so they do not push out of the caches the lines just written
-// for the next phase (on a 2^24 transform, whose three 128 MB buffers
-// overflow the 256 MB MALL, this keeps Phase III's input resident: measured
-// 13% faster end to end; the same hint on other phases' loads or on stores
-// measured slower).
+// Loads of data the transform never reads again: non-temporal, so they do not
+// push out of the caches the lines just written for the next pass (on a 2^24
+// transform, whose three 128 MB buffers overflow the 256 MB MALL, this keeps
+// Phase III's input resident: the packed form 13% faster end to end).  Where
+// tiles share lines (runs below 128 bytes) the hint costs more than it gives:
+// 2^22 in the direct form 34 -> 41 us.  The symmetric form's choices: SymTemporal
+// in sym.hip.
 typedef float nt_f2 __attribute__((ext_vector_type(2)));
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float2 ld2_last(const float2 *p)
@@ -109,16 +110,17 @@ __device__ __forceinline__ float4 ld4_last(const float2 *p)
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// Store of an item.  COH: a device-coherent store (written through this
-// XCD's L2), for results another workgroup of the same launch reads after a
-// completion counter says they are there.
-__device__ __forceinline__ float2 ld2_nt(const float2 *p, bool nt) { return nt ? ld2_last(p) : *p; }  // nt: a constant
+// With nt (a compile-time constant at every call) the non-temporal access.
+__device__ __forceinline__ float2 ld2_nt(const float2 *p, bool nt) { return nt ? ld2_last(p) : *p; }
 __device__ __forceinline__ void st2_nt(float2 *p, float2 v, bool nt)
 {
     if (nt) st2_stream(p, v);
     else *p = v;
 }
 
+// Store of an item.  COH: a device-coherent store (written through this
+// XCD's L2), for results another workgroup of the same launch reads after a
+// completion counter says they are there.
 template <bool COH>
 __device__ __forceinline__ void st2(char *p, float2 v)
 {
