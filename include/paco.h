@@ -153,7 +153,8 @@ paco_status paco_plan_create_ex(paco_plan **plan, int64_t N1, int64_t N2, int64_
 paco_status paco_plan_workspace_size(const paco_plan *plan, size_t *bytes);
 
 /* Runs Phase I (in -> workspace), Phase II (workspace -> out) and Phase III
- * (out -> out, in place) on `stream` (a hipStream_t; NULL = default stream).
+ * (out -> out, in place; the forms below divide the same arithmetic
+ * differently) on `stream` (a hipStream_t; NULL = default stream).
  * in == out is allowed.  in, out and workspace are device pointers, 16-byte
  * aligned (kernels move two complex64 items per 16-byte access), of N1*N2 complex64 each (workspace: at least the reported size).
  *
@@ -211,7 +212,24 @@ paco_status paco_plan_workspace_size(const paco_plan *plan, size_t *bytes);
  * 32-point transform over rr, and pass 3 transforms rows 32 t + q0 into
  * out[(q0 + 32 q)*N1 + v]; pass 1 is the same.  paco_plan_has_split
  * reports 2; the option PACO_PLAN_NO_SYM keeps the split form of Phase I
- * alone. */
+ * alone.
+ *
+ * Direct form and balanced shapes.  On one HBM a shape N1 x N2 is a view of
+ * the same vector, and Lemma 1 holds for any split, so a PACO_C64 plan without
+ * options (PACO_PLAN_MIXED apart) runs the split of N that is the fastest:
+ *   N <= 2^14: one launch of one workgroup (the workspace is not used);
+ *   2^15 <= N <= 2^23: two column passes, in -> workspace -> out, of
+ *     2^ceil(l/2) and 2^floor(l/2) points, l = log2 N; plans with N1 >= 2^12,
+ *     N2 >= 64 and N <= 2^20 run their split form instead;
+ *   N >= 2^24: a shape without a symmetric form runs the passes of
+ *     2^floor(l/2) x 2^ceil(l/2), at 2^28 of 8192 x 32768, and so does
+ *     16384 x 16384.
+ * Neither N1, N2, b nor p then enters the result.  The split MFMA forms run two
+ * column passes of their own lengths with N1 and N2 both in [2^7, 2^11].  The
+ * stage hooks of paco_execute_stage run the phases (or the split or symmetric
+ * passes) of the plan's own shape in every case; where paco_execute runs
+ * another split the two agree within rounding.  paco_plan_describe names what
+ * runs ("direct[...]", "executes ...") and counts its launches. */
 paco_status paco_execute(const paco_plan *plan, const void *in, void *out, void *workspace,
                          size_t workspace_bytes, void *stream);
 
@@ -246,10 +264,13 @@ paco_status paco_execute_noalloc(const paco_plan *plan, const void *in, void *ou
  * creation; a square plan reuses its own), so its input slabs are exactly
  * those output slabs and its output slabs, columns of the N1 x N2 matrix X,
  * are exactly the forward input's: the ownership is restored by the inverse
- * itself, with no further exchange.  The arithmetic is conj(Omega_N conj(y))
- * / N, the two conjugations and the 1/N scale (a power of two, exact) folded
- * into Phase I's loads and Phase III's stores: the same launches as
- * paco_execute.  All dtypes.  Returns PACO_ERR_UNSUPPORTED (the forward
+ * itself, with no further exchange.  Where paco_execute runs a split of N of
+ * the library's own (direct form, balanced shapes), and for the non-square
+ * symmetric shapes, the inverse runs that split too: on one HBM both
+ * ownerships are views of the natural-order vector.  The arithmetic is
+ * conj(Omega_N conj(y)) / N, the two conjugations and the 1/N scale (a power
+ * of two, exact) folded into the first pass's loads and the last one's
+ * stores.  All dtypes.  Returns PACO_ERR_UNSUPPORTED (the forward
  * plan still works) if the N2 x N1 passes could not be built at plan
  * creation (e.g. device memory for their tables). */
 paco_status paco_execute_inverse(const paco_plan *plan, const void *in, void *out, void *workspace,
@@ -276,9 +297,9 @@ paco_status paco_execute_two_pass(const paco_plan *plan, const void *in, void *o
 /* *yes = 1 when paco_execute_two_pass runs for this plan, else 0. */
 paco_status paco_plan_has_two_pass(const paco_plan *plan, int32_t *yes);
 
-/* *yes = 2 when paco_execute (and paco_execute_inverse of a square plan)
- * runs the symmetric split form for this plan, 1 for the split form of
- * Phase I alone, else 0. */
+/* *yes = 2 when the plan's shape has the symmetric split form, 1 for the
+ * split form of Phase I alone, else 0: the passes PACO_SPLIT runs one by one,
+ * and those of paco_execute unless that runs another split (see there). */
 paco_status paco_plan_has_split(const paco_plan *plan, int32_t *yes);
 
 /* Runs one phase alone, for stage-wise checks and per-phase timing, always
@@ -319,21 +340,23 @@ paco_status paco_plan_destroy(paco_plan *plan);
 
 /* ---- batched form ---------------------------------------------------------
  * Many independent transforms, transform i of N[i] = 2^k items (2 <= k <= 20),
- * each computed as y_i = Omega_{N_i} x_i through the same three phases
- * (section 3) with its own factorisation N_i = N1 * N2, base b and tile
- * widths, all inside ONE kernel launch (a persistent grid that takes tiles
- * from a work queue).  Layout: the transforms are packed back to back, x_i at
- * items [off_i, off_i + N[i]) of `in`, off_i = N[0] + ... + N[i-1]; y_i is
+ * each computed as y_i = Omega_{N_i} x_i in the direct form of paco_execute
+ * (one workgroup up to 2^14 items, two column passes of N_i = N1 * N2 above),
+ * all inside ONE kernel launch: a persistent grid that takes tiles from a work
+ * queue, or, without transforms above 2^14 items, one workgroup per task.  With
+ * the default splits y_i has the bits of the single plan.  Layout: the
+ * transforms are packed back to back, x_i at items [off_i, off_i + N[i]) of `in`, off_i = N[0] + ... + N[i-1]; y_i is
  * written in natural order at the same items of `out`.
  */
 typedef struct paco_batch_plan_s paco_batch_plan;
 
 /* Plans `count` transforms of sizes N[0..count-1] (copied; the caller keeps
- * N).  The per-size choices (N1 = 2^l1 with N2 = N/N1, b in {2, 4, 16}
- * dividing both exponents, tile widths) come from, in order: the tuning
- * cache file tune_cache_path (text, one line per size, written by an earlier
- * call), else timing every candidate on the current device (allocates about
- * 400 MB of device memory for a moment; the option PACO_BATCH_NO_TUNE of
+ * N).  The per-size choice that matters, N1 = 2^l1 with N2 = N/N1 above 2^14
+ * items (b is reported only), comes from, in order: the tuning cache file
+ * tune_cache_path (text, one line per size, written by an earlier call; a line
+ * whose N1 or N2 is outside [2^7, 2^10] is ignored above 2^14 items, its tile
+ * fields are not used), else timing every candidate on the current device
+ * (allocates about 400 MB of device memory for a moment; the option PACO_BATCH_NO_TUNE of
  * paco_batch_plan_create_ex skips the timing and takes the defaults), after which
  * the cache file, if named, is (re)written.  NULL: tune now, no file.
  * dt must be PACO_C64 (the split MFMA forms are single-transform only).
@@ -375,7 +398,7 @@ paco_status paco_batch_workspace_size(const paco_batch_plan *bp, size_t *bytes);
  * kernel and no memset or allocation, so it may be captured into a HIP
  * graph and replayed.  Executions of one batch plan must not overlap in
  * time (they share the plan's work-queue counters): issue them on one
- * stream.  A completion wait that exceeds its poll limit is counted (see
+ * stream.  (The plain launch of short transforms has no counters.)  A completion wait that exceeds its poll limit is counted (see
  * paco_batch_errors) instead of hanging; the launch then still completes,
  * with unspecified results.  The limit is 2^22 polls; the option spin_limit
  * of paco_batch_plan_create_ex sets another (testing). */

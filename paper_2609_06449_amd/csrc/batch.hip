@@ -719,6 +719,13 @@ void free_plan(paco_batch_plan_s *P)
 // the persistent kernel; the fastest of three timed launches wins.
 paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
 {
+    bool choice = false;
+    for (int k : ks) {
+        const std::vector<SizePlan> cand = paco::candidates(k);
+        plans[k] = cand.front();
+        choice = choice || cand.size() > 1;
+    }
+    if (!choice) return PACO_OK;
     const int64_t items = int64_t(1) << 24;
     void *buf = nullptr;
     hipError_t e = hipMalloc(&buf, size_t(items) * 8 * 3);
@@ -736,7 +743,6 @@ paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
         const int64_t copies = std::min<int64_t>(std::max<int64_t>(1, items >> k), 16384);
         float best = 1e30f;
         const std::vector<SizePlan> cand = paco::candidates(k);
-        plans[k] = cand.front();
         if (cand.size() == 1) continue;
         for (const SizePlan &sp : cand) {
             paco_batch_plan_s *T = new (std::nothrow) paco_batch_plan_s();
