@@ -117,15 +117,17 @@ __device__ __forceinline__ void mf_load_ops(const float2 (&it)[4], float (&x)[8]
     }
 }
 
-// Non-temporal accesses (the reasons in sym.hip, SymTemporal): pass 1 reads
-// x with last-use loads; at L = 256 it stores ws plainly and pass 3 reads W
-// with last-use loads, at L = 512 it streams ws and pass 3 streams y.  us per
-// transform on buffers that no cache holds, against plain accesses but a
-// streamed ws, FP16x3 / BF16x3 / BF16x6: 4096^2 184 / 179 / 188 -> 169 / 161 /
-// 169 (one set of buffers over and over 152 / 149 / 159 -> 153 / 150 / 156),
-// 8192^2 717 / 697 / 726 -> 705 / 693 / 728.
-// Pass 1 (see sym.hip): stage 1 butterfly (cl = n, jl = 4 w + G) over jh,
-// stage 2 butterfly (kl = n, cl = 4 w + G) over jl.
+// Non-temporal accesses (the reasons in sym.hip, SymTemporal), us per transform
+// on buffers that no cache holds, FP16x3 / BF16x3 / BF16x6:
+//   L = 256: pass 1 reads x with last-use loads and stores ws plainly, pass 3
+//   reads W with last-use loads: 184 / 179 / 188 -> 169 / 161 / 169 (one set of
+//   buffers over and over 152 / 149 / 159 -> 153 / 150 / 156);
+//   L = 512: ws is streamed; FP16x3 also reads x with last-use loads and streams
+//   y (705.6 -> 700.2), which the other two do not gain from (689.5 -> 694.3,
+//   713.6 -> 724.7).
+template <int PREC>
+constexpr bool kLongNt = PREC == kPrecFP16x3;
+
 template <int PREC>
 __global__ __launch_bounds__(256) void sym_first_mf_kernel(SymPass P)
 {
@@ -394,8 +396,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PREC == kPr
         for (int G = 0; G < 4; ++G) {
             const uint32_t base = addr::sym1_load_base(N2, blk, uint32_t(n + 16 * (4 * w + G)));
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                it[G][k] = ld2_last(off32(P.src, base + addr::sym1_load_off(N2, uint32_t(8 * half + (comp ? 4 + k : k)), LL)));
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t i = uint32_t(8 * half + (comp ? 4 + k : k));
+                if constexpr (kLongNt<PREC>)
+                    it[G][k] = ld2_last(off32(P.src, base + addr::sym1_load_off(N2, i, LL)));
+                else
+                    it[G][k] = *off32(P.src, base + addr::sym1_load_off(N2, i, LL));
+            }
         }
     };
     int e = 0;  // FP16x3: the tile's scale, from stage A to the stores
@@ -528,9 +535,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void s
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float2 y = o[kc][i];
-                    st2_stream(off32(P.dst, d + addr::sym3_store_off(N1, uint32_t(4 * kb + i))),
-                               P.out_scale != 0.f ? conj_scale(y, P.out_scale * osc)
-                                                  : make_float2(y.x * osc, y.y * osc));
+                    const float2 z =
+                        P.out_scale != 0.f ? conj_scale(y, P.out_scale * osc) : make_float2(y.x * osc, y.y * osc);
+                    if constexpr (kLongNt<PREC>)
+                        st2_stream(off32(P.dst, d + addr::sym3_store_off(N1, uint32_t(4 * kb + i))), z);
+                    else
+                        *off32(P.dst, d + addr::sym3_store_off(N1, uint32_t(4 * kb + i))) = z;
                 }
             }
         }
