@@ -28,13 +28,14 @@ namespace {
 // against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
 // 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
 constexpr int kLT = 2;
-// 4096-point columns (2^23 only): two LDS groups of two columns, 64 KiB, so
-// two workgroups share a CU.  2^23: 80 us; the three-pass forms it replaces
-// took 95 to 130 by shape.  2^24 in two passes took 191 us against 162 (now
-// 132) for the symmetric form's three, which ends the range.
+// 4096-point columns (pass A of 2^23 only): 8 columns in two LDS groups, 1024
+// threads and 136 KiB, whose 64-byte runs are read last-use (pass_a_tile).
+// 2^23: 72 us, with 4 columns and two workgroups per CU 79; the three-pass forms
+// it replaces took 95 to 130 by shape.  2^24 in two passes of 4 columns took 191
+// us against 162 (now 132) for the symmetric form's three, which ends the range.
 constexpr int groups(int l) { return l == 12 ? 2 : 1; }
 // (the split MFMA forms' butterflies need full waves: 8 columns of 128 points)
-__host__ __device__ constexpr int tile_cols(int l, int prec) { return prec != kPrecFP32 && l == 7 ? 3 : kLT; }
+__host__ __device__ constexpr int tile_cols(int l, int prec) { return l == 12 || (prec != kPrecFP32 && l == 7) ? 3 : kLT; }
 
 template <int L, int PREC>
 __global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC), groups(L))) void direct_a_kernel(DirectArgs P)
@@ -60,8 +61,13 @@ void launch_pass(bool b, int lcols, const DirectArgs &a, hipStream_t s)
 {
     constexpr int LT = tile_cols(L, PREC);
     const dim3 tiles(1u << (lcols - LT)), threads(tile_threads(L, LT, groups(L)));
-    if (b) hipLaunchKernelGGL((direct_b_kernel<L, PREC>), tiles, threads, 0, s, a);
-    else hipLaunchKernelGGL((direct_a_kernel<L, PREC>), tiles, threads, 0, s, a);
+    if constexpr (L < 12) {  // 4096 points: pass A only
+        if (b) {
+            hipLaunchKernelGGL((direct_b_kernel<L, PREC>), tiles, threads, 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((direct_a_kernel<L, PREC>), tiles, threads, 0, s, a);
 }
 
 // one pass of 2^l points over 2^lcols columns
@@ -76,11 +82,9 @@ hipError_t direct_pass_t(bool b, int l, int lcols, const DirectArgs &a, hipStrea
     case 11: launch_pass<11, PREC>(b, lcols, a, s); break;
     case 12:
         // split butterflies at 4096 points spilled and took 209 us at 2048 x 4096, the three-pass form 175
-        if constexpr (PREC == kPrecFP32) {
-            launch_pass<12, PREC>(b, lcols, a, s);
-            break;
-        }
-        return hipErrorInvalidValue;
+        if (PREC != kPrecFP32 || b) return hipErrorInvalidValue;
+        if constexpr (PREC == kPrecFP32) launch_pass<12, PREC>(false, lcols, a, s);
+        break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
