@@ -107,7 +107,11 @@ struct BatchArgs {
 // (kept live across the others, it spilled).
 __device__ __forceinline__ int own(int tid) { return int(opaque(uint32_t(tid))); }
 
-constexpr int pass_lt(int l) { return kTileLog2 - l; }
+// Columns (log2) of a pass tile of 2^l points.  The shared queue serves few
+// large transforms, which a full tile leaves on too few workgroups: half a
+// tile there, 16 items per thread in one group (one transform of 2^16 32 -> 22
+// us, of 2^20 35 -> 30, nine of 2^20 117 -> 95).
+constexpr int pass_lt(int l, bool coh) { return (coh ? kTileLog2 - 1 : kTileLog2) - l; }
 // transforms of 2^l points a small task of 2^lw threads holds: 16 items per
 // thread (shorter ones: one transform per thread)
 constexpr int small_lt(int l, int lw) { return l < 4 ? lw : lw + 4 - l; }
@@ -124,7 +128,7 @@ constexpr int batch_lds()
 {
     int m = tile_lds(13, 1, 2);  // kOne
     for (int l = kBatchMinLog2; l <= 13; ++l) m = m < tile_lds(l, small_lt(l, kLogBT), 1) ? tile_lds(l, small_lt(l, kLogBT), 1) : m;
-    for (int l = kPassMin; l <= kPassMax; ++l) m = m < tile_lds(l, pass_lt(l), 2) ? tile_lds(l, pass_lt(l), 2) : m;
+    for (int l = kPassMin; l <= kPassMax; ++l) m = m < tile_lds(l, pass_lt(l, false), 2) ? tile_lds(l, pass_lt(l, false), 2) : m;
     return m;
 }
 static_assert(2 * (batch_lds() * 8 + 16) <= 160 * 1024, "two workgroups per CU");
@@ -194,16 +198,18 @@ __global__ __launch_bounds__(1 << LW) void batch_small_kernel(BatchArgs A)
 template <int L, bool COH>
 __device__ __forceinline__ void run_a_len(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
 {
-    static_assert(tile_threads(L, pass_lt(L), 2) == kBT, "tile geometry");
-    pass_a_tile<L, pass_lt(L), 2, COH>(A.in + J.base, A.ws + J.base, J.l2, pass_lt(J.l2), tile << pass_lt(L),
-                                       A.stw + A.stw_off[L], smem, own(tid), false);
+    constexpr int LT = pass_lt(L, COH), H = COH ? 1 : 2;
+    static_assert(tile_threads(L, LT, H) == kBT, "tile geometry");
+    pass_a_tile<L, LT, H, COH>(A.in + J.base, A.ws + J.base, J.l2, pass_lt(J.l2, COH), tile << LT, A.stw + A.stw_off[L],
+                               smem, own(tid), false);
 }
 
-template <int L>
+template <int L, bool COH>
 __device__ __forceinline__ void run_b_len(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
 {
-    pass_b_tile<L, pass_lt(L), 2>(A.ws + J.base, A.out + J.base, J.l1, tile << pass_lt(L), A.tabs[J.tab],
-                                  A.stw + A.stw_off[L], smem, own(tid), 0.f);
+    constexpr int LT = pass_lt(L, COH), H = COH ? 1 : 2;
+    pass_b_tile<L, LT, H>(A.ws + J.base, A.out + J.base, J.l1, tile << LT, A.tabs[J.tab], A.stw + A.stw_off[L], smem,
+                          own(tid), 0.f);
 }
 
 template <bool COH>
@@ -217,13 +223,14 @@ __device__ __forceinline__ void run_a(const BatchArgs &A, const BatchJob &J, uin
     }
 }
 
+template <bool COH>
 __device__ __forceinline__ void run_b(const BatchArgs &A, const BatchJob &J, uint32_t tile, float2 *smem, int tid)
 {
     switch (J.l2) {
-    case 7: run_b_len<7>(A, J, tile, smem, tid); break;
-    case 8: run_b_len<8>(A, J, tile, smem, tid); break;
-    case 9: run_b_len<9>(A, J, tile, smem, tid); break;
-    default: run_b_len<10>(A, J, tile, smem, tid); break;
+    case 7: run_b_len<7, COH>(A, J, tile, smem, tid); break;
+    case 8: run_b_len<8, COH>(A, J, tile, smem, tid); break;
+    case 9: run_b_len<9, COH>(A, J, tile, smem, tid); break;
+    default: run_b_len<10, COH>(A, J, tile, smem, tid); break;
     }
 }
 
@@ -277,7 +284,7 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void b
         }
         switch (J.kind) {
         case kPassA: run_a<COH>(A, J, task.tile, smem, tid); break;
-        case kPassB: run_b(A, J, task.tile, smem, tid); break;
+        case kPassB: run_b<COH>(A, J, task.tile, smem, tid); break;
         case kOne: run_one(A, J, smem, tid); break;
         default: run_small<kLogBT>(A, J, smem, tid); break;
         }
@@ -544,10 +551,10 @@ paco_status build_batch(paco_batch_plan_s *P)
             const int32_t first = int32_t(jobs.size());
             BatchJob a = J, c = J;
             a.kind = kPassA;
-            a.ntiles = 1 << (sp.l2 - pass_lt(sp.l1));
+            a.ntiles = 1 << (sp.l2 - pass_lt(sp.l1, P->coh));
             a.signal = 1;
             c.kind = kPassB;
-            c.ntiles = 1 << (sp.l1 - pass_lt(sp.l2));
+            c.ntiles = 1 << (sp.l1 - pass_lt(sp.l2, P->coh));
             c.dep = first;
             c.dep_tiles = a.ntiles;
             jobs.push_back(a);
