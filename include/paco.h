@@ -353,9 +353,10 @@ typedef struct paco_batch_plan_s paco_batch_plan;
 /* Plans `count` transforms of sizes N[0..count-1] (copied; the caller keeps
  * N).  The per-size choice that matters, N1 = 2^l1 with N2 = N/N1 above 2^14
  * items (b is reported only), comes from, in order: the tuning cache file
- * tune_cache_path (text, one line per size, written by an earlier call; a line
- * whose N1 or N2 is outside [2^7, 2^10] is ignored above 2^14 items, its tile
- * fields are not used), else timing every candidate on the current device
+ * tune_cache_path (text, one line per size, written by an earlier call on the
+ * same device model by a library with the same kernels, which its key line
+ * names, else ignored; a line whose N1 or N2 is outside [2^7, 2^10] is ignored
+ * above 2^14 items), else timing every candidate on the current device
  * (allocates about 400 MB of device memory for a moment; the option PACO_BATCH_NO_TUNE of
  * paco_batch_plan_create_ex skips the timing and takes the defaults), after which
  * the cache file, if named, is (re)written.  NULL: tune now, no file.

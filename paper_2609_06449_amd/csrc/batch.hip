@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(4))) void b
 // Host side
 // ---------------------------------------------------------------------------
 struct SizePlan {
-    int l1 = 0, l2 = 0, t = 1, v1 = 0, v3 = 0;
+    int l1 = 0, l2 = 0, t = 1;
 };
 
 int ilog2_pow2(int64_t n)
@@ -348,10 +348,10 @@ std::vector<SizePlan> candidates(int k)
     std::vector<SizePlan> out;
     const int mid = (k + 1) / 2;
     const int lo = std::max(kPassMin, k - kPassMax), hi = std::min(kPassMax, k - kPassMin);
-    out.push_back({mid, k - mid, 1, 0, 0});
+    out.push_back({mid, k - mid, 1});
     if (k > kChipMaxLog2)
         for (int l = lo; l <= hi; ++l)
-            if (l != mid) out.push_back({l, k - l, 1, 0, 0});
+            if (l != mid) out.push_back({l, k - l, 1});
     return out;
 }
 
@@ -721,9 +721,9 @@ void free_plan(paco_batch_plan_s *P)
 }
 
 // ---- autotuner -----------------------------------------------------------------
-// For every transform size of the batch, each candidate (split, b, tile
-// variants) runs a batch of copies of that size (about 2^24 items) through
-// the persistent kernel; the fastest of three timed launches wins.
+// For every transform size of the batch, each candidate split runs a batch of
+// copies of that size (about 2^24 items) through the persistent kernel; the
+// fastest of three timed launches wins.
 paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
 {
     bool choice = false;
@@ -789,8 +789,7 @@ paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
 }
 
 // A cached plan is used if its split is one of the candidates' (any split of
-// a transform of one workgroup) and its b is a base of both sides; the last
-// two fields are tile variants of an earlier kernel and have no effect.
+// a transform of one workgroup) and its b is a base of both sides.
 bool valid_plan(int k, const SizePlan &sp)
 {
     if (sp.t != 1 && sp.t != 2 && sp.t != 4) return false;
@@ -801,8 +800,11 @@ bool valid_plan(int k, const SizePlan &sp)
     return false;
 }
 
-// The device a tuning cache was measured on: its entries are reused only on
-// the same architecture, CU count and cache format.
+// The device and the kernels a tuning cache was measured on: its entries are
+// reused only on the same architecture and CU count, and only while format
+// stands.  A change of the passes that the candidates are timed on takes a new
+// number, also where the lines look the same (format 1: three phases per
+// transform, whose timings say nothing about the two column passes).
 std::string cache_key()
 {
     int dev = 0;
@@ -811,10 +813,10 @@ std::string cache_key()
     std::string arch = prop.gcnArchName;
     for (char &ch : arch)
         if (ch == ' ') ch = '_';
-    return arch + " cus=" + std::to_string(prop.multiProcessorCount) + " format=1";
+    return arch + " cus=" + std::to_string(prop.multiProcessorCount) + " format=2";
 }
 
-// Tuning cache: a "key <device key>" line, then lines "log2N l1 l2 t v1 v3";
+// Tuning cache: a "key <device key>" line, then lines "log2N l1 l2 t";
 // '#' starts a comment.  A file with another key (or none) is ignored, and
 // rewritten after tuning.
 void read_cache(const char *path, const std::string &key, std::map<int, SizePlan> &plans)
@@ -832,7 +834,7 @@ void read_cache(const char *path, const std::string &key, std::map<int, SizePlan
         std::istringstream is(line);
         int k;
         SizePlan sp;
-        if (is >> k >> sp.l1 >> sp.l2 >> sp.t >> sp.v1 >> sp.v3)
+        if (is >> k >> sp.l1 >> sp.l2 >> sp.t)
             if (k >= paco::kBatchMinLog2 && k <= paco::kBatchMaxLog2 && valid_plan(k, sp)) plans[k] = sp;
     }
 }
@@ -841,11 +843,10 @@ bool write_cache(const char *path, const std::string &key, const std::map<int, S
 {
     std::ofstream f(path);
     if (!f) return false;
-    f << "# paco batched plan cache: log2N l1 l2 t v1 v3 (N1 = 2^l1, N2 = 2^l2, b = 2^t, tile variants)\n";
+    f << "# paco batched plan cache: log2N l1 l2 t (N1 = 2^l1, N2 = 2^l2, b = 2^t)\n";
     f << "key " << key << '\n';
     for (auto &kv : plans)
-        f << kv.first << ' ' << kv.second.l1 << ' ' << kv.second.l2 << ' ' << kv.second.t << ' ' << kv.second.v1 << ' '
-          << kv.second.v3 << '\n';
+        f << kv.first << ' ' << kv.second.l1 << ' ' << kv.second.l2 << ' ' << kv.second.t << '\n';
     return bool(f);
 }
 
