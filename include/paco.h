@@ -219,12 +219,13 @@ paco_status paco_plan_workspace_size(const paco_plan *plan, size_t *bytes);
  * options (PACO_PLAN_MIXED apart) runs the split of N that is the fastest:
  *   N <= 2^14: one launch of one workgroup (the workspace is not used);
  *   2^15 <= N <= 2^23: two column passes, in -> workspace -> out, of
- *     2^ceil(l/2) and 2^floor(l/2) points, l = log2 N; plans with N1 >= 2^12,
- *     N2 >= 64 and N <= 2^20 run their split form instead;
+ *     2^ceil(l/2) and 2^floor(l/2) points, l = log2 N, or of N1 and N2 points
+ *     where both lie in [2^8, 2^10] (at 2^15 in [2^7, 2^8]); plans with N1 >=
+ *     2^12, N2 >= 64 and N <= 2^20 run their split form instead;
  *   N >= 2^24: a shape without a symmetric form runs the passes of
  *     2^floor(l/2) x 2^ceil(l/2), at 2^28 of 8192 x 32768, and so does
  *     16384 x 16384.
- * Neither N1, N2, b nor p then enters the result.  The split MFMA forms run two
+ * b and p never enter the result, N1 and N2 only as said above.  The split MFMA forms run two
  * column passes of their own lengths with N1 and N2 both in [2^7, 2^11].  The
  * stage hooks of paco_execute_stage run the phases (or the split or symmetric
  * passes) of the plan's own shape in every case; where paco_execute runs
@@ -343,8 +344,9 @@ paco_status paco_plan_destroy(paco_plan *plan);
  * each computed as y_i = Omega_{N_i} x_i in the direct form of paco_execute
  * (one workgroup up to 2^14 items, two column passes of N_i = N1 * N2 above),
  * all inside ONE kernel launch: a persistent grid that takes tiles from a work
- * queue, or, without transforms above 2^14 items, one workgroup per task.  With
- * the default splits y_i has the bits of the single plan.  Layout: the
+ * queue, or, without transforms above 2^14 items, one workgroup per task.  y_i has
+ * the bits of paco_execute of a plan with the N1, N2, p and b that
+ * paco_batch_plan_describe reports for it, tuned or not.  Layout: the
  * transforms are packed back to back, x_i at items [off_i, off_i + N[i]) of `in`, off_i = N[0] + ... + N[i-1]; y_i is
  * written in natural order at the same items of `out`.
  */
@@ -355,8 +357,8 @@ typedef struct paco_batch_plan_s paco_batch_plan;
  * items (b is reported only), comes from, in order: the tuning cache file
  * tune_cache_path (text, one line per size, written by an earlier call on the
  * same device model by a library with the same kernels, which its key line
- * names, else ignored; a line whose N1 or N2 is outside [2^7, 2^10] is ignored
- * above 2^14 items), else timing every candidate on the current device
+ * names, else ignored; above 2^14 items a line is ignored unless N1 and N2 are
+ * in [2^8, 2^10], at 2^15 items in [2^7, 2^8]), else timing every candidate on the current device
  * (allocates about 400 MB of device memory for a moment; the option PACO_BATCH_NO_TUNE of
  * paco_batch_plan_create_ex skips the timing and takes the defaults), after which
  * the cache file, if named, is (re)written.  NULL: tune now, no file.

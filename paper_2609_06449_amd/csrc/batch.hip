@@ -47,9 +47,9 @@ namespace {
 constexpr int kBT = 512;             // threads per workgroup of the persistent kernel
 constexpr int kBatchMinLog2 = 2;     // N >= 4 (N1, N2 >= 2)
 constexpr int kBatchMaxLog2 = 20;    // pass lengths <= 2^10
-constexpr int kChipMaxLog2 = 14;     // whole transform inside one workgroup
+constexpr int kChipMaxLog2 = kDirectChipLog2;  // whole transform inside one workgroup
 constexpr int kTileLog2 = 14;        // items of a pass tile: 32 per thread, in two groups
-constexpr int kPassMin = 7, kPassMax = 10;
+constexpr int kPassMin = 7, kPassMax = kBatchPassMax;
 constexpr uint32_t kSpinLimit = 1u << 22;
 // s_waitcnt operand that waits for vmcnt = 0 only (gfx9 encoding: vmcnt in
 // bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima)
@@ -347,11 +347,9 @@ std::vector<SizePlan> candidates(int k)
 {
     std::vector<SizePlan> out;
     const int mid = (k + 1) / 2;
-    const int lo = std::max(kPassMin, k - kPassMax), hi = std::min(kPassMax, k - kPassMin);
     out.push_back({mid, k - mid, 1});
-    if (k > kChipMaxLog2)
-        for (int l = lo; l <= hi; ++l)
-            if (l != mid) out.push_back({l, k - l, 1});
+    for (int l = kPassMin; l <= kPassMax; ++l)
+        if (l != mid && batch_split(l, k - l)) out.push_back({l, k - l, 1});
     return out;
 }
 

@@ -36,13 +36,13 @@ void chip(const DirectArgs &a, hipStream_t s)
 
 }  // namespace
 
-DirectForm direct_form(int log2N)
+DirectForm direct_form(int l1, int l2)
 {
     DirectForm f{};
-    f.log2N = log2N;
-    if (log2N <= kDirectChipLog2) return f;
-    f.l1 = (log2N + 1) / 2;
-    f.l2 = log2N / 2;
+    f.log2N = l1 + l2;
+    if (f.log2N <= kDirectChipLog2) return f;
+    f.l1 = batch_split(l1, l2) ? l1 : (f.log2N + 1) / 2;
+    f.l2 = f.log2N - f.l1;
     return f;
 }
 

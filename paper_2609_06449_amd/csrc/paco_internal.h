@@ -208,11 +208,27 @@ struct SymPass {
 
 // The direct form (direct.hip), FP32, N <= 2^23: one launch of one workgroup
 // up to 2^14 items, else two column passes over N = 2^l1 2^l2 (tile.h).  The
-// split of N is the library's own: neither N1 x N2 nor b nor p of the plan
-// enters the result.  The split MFMA forms run the two passes too, of the
-// lengths N1 and N2 of the plan (2^7 .. 2^11 each).
+// split of N is the library's own, the balanced one, except that a plan whose
+// N1 x N2 is a split that the batched kernel may run (batch_split) runs just
+// that: the batched transform has the single plan's bits whatever its tuner
+// picked.  Otherwise neither N1 x N2 nor b nor p of the plan enters the result.
+// The split MFMA forms run the two passes too, of the lengths N1 and N2 of the
+// plan (2^7 .. 2^11 each).
 constexpr int kDirectChipLog2 = 14;  // the largest transform of one workgroup
 constexpr int kDirectMaxLog2 = 23;
+constexpr int kBatchPassMax = 10;    // pass lengths of the batched kernel: up to 2^10
+// The splits of N = 2^15 .. 2^20 that the batched form's tuner chooses from.
+// Passes of 2^8 .. 2^10 points, 2^7 only at 2^15, where every split has one: a
+// single plan's 4-column tile of 128 points is half a wave.  us per call as
+// balanced / as N1 x N2: 256 x 1024 10.6 / 10.5, 1024 x 256 10.6 / 10.7, 512 x 1024 12.6 /
+// 12.0, 128 x 256 8.8 / 8.9, all within a run's noise; but 512 x 128 8.8 / 9.0 and
+// 1024 x 128 9.0 / 9.9, for which a large batch gave nothing back (512 of 2^17
+// 384 / 386 us, 1024 of 2^16 374 / 369).
+constexpr bool batch_split(int l1, int l2)
+{
+    return l1 + l2 > kDirectChipLog2 && l1 <= kBatchPassMax && l2 <= kBatchPassMax &&
+           ((l1 >= 8 && l2 >= 8) || (l1 + l2 == 15 && l1 >= 7 && l2 >= 7));
+}
 struct DirectForm {
     int32_t log2N, l1, l2;           // two passes: pass A 2^l1 points over 2^l2 columns, pass B the reverse (else 0)
     int32_t prec;                    // radix-16 butterflies of the two passes (paco_dtype)
@@ -258,8 +274,8 @@ LocalLaunch local_fft_geometry(const LocalPass &p);
 hipError_t local_fft_prepare();  // raises the dynamic-LDS limit of every kernel once
 hipError_t launch_local_fft(const LocalPass &p, hipStream_t s);
 hipError_t launch_middle(const MiddlePass &p, hipStream_t s);
-// The direct form's split of N = 2^log2N (tables unset).
-DirectForm direct_form(int log2N);
+// The direct form's split of N = 2^l1 2^l2 (tables unset).
+DirectForm direct_form(int l1, int l2);
 // Kernel launches of the form.
 inline int direct_launches(const DirectForm &f) { return f.l1 == 0 ? 1 : 2; }
 // The whole transform on stream s: in -> ws -> out (one workgroup: in -> out).

@@ -309,7 +309,7 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
             P->direct_form.l2 = P->l2;
             P->direct_form.prec = int32_t(dt);
         } else {
-            P->direct_form = paco::direct_form(P->lN);
+            P->direct_form = paco::direct_form(P->l1, P->l2);
         }
         if (P->direct_form.l1) {
             const int64_t n = int64_t(16) << P->direct_form.l1;
@@ -681,7 +681,7 @@ paco_status create_with_inverse(paco_plan **plan, int64_t N1, int64_t N2, int64_
     if (opt.cols_long < 0 || (opt.cols_long > 0 && ilog2_exact(opt.cols_long) < 0))
         return fail(PACO_ERR_INVALID_ARG, "cols_long must be 0 (default) or a power of two");
     paco_status st = create_impl(plan, N1, N2, p, b, dt, opt);
-    if (st != PACO_OK || (*plan)->direct) return st;  // (the direct form's split of N is its own)
+    if (st != PACO_OK || (*plan)->direct) return st;  // (the inverse runs the same passes)
     const std::string note = g_last_error;
     // FP32 from 2^24 items on: the shape of N whose three passes of the
     // symmetric form are the fastest, the balanced one and 8192 x 32768 at
