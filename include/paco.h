@@ -355,7 +355,7 @@ typedef struct paco_batch_plan_s paco_batch_plan;
 /* Plans `count` transforms of sizes N[0..count-1] (copied; the caller keeps
  * N).  The per-size choice that matters, N1 = 2^l1 with N2 = N/N1 above 2^14
  * items (b is reported only), comes from, in order: the tuning cache file
- * tune_cache_path (text, one line per size, written by an earlier call on the
+ * tune_cache_path (text, one line per size and queue mode, written by an earlier call on the
  * same device model by a library with the same kernels, which its key line
  * names, else ignored; above 2^14 items a line is ignored unless N1 and N2 are
  * in [2^8, 2^10], at 2^15 items in [2^7, 2^8]), else timing every candidate on the current device

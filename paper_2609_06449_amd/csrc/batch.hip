@@ -436,6 +436,46 @@ int queue_count(const paco_batch_options &opt)
     return (nx >= 1 && nx <= paco::kMaxQueues) ? nx : 1;
 }
 
+// Deals the transforms to the work queues, largest first onto the least loaded
+// (returned queue by queue), and sets which kernel runs them (lw, nq, coh).
+std::vector<std::vector<int32_t>> deal_queues(paco_batch_plan_s *P)
+{
+    using namespace paco;
+    int nx = queue_count(P->opt);
+    int dev = 0, nxcd = 1;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&nxcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess)
+        nxcd = 0;  // unknown: one shared, coherent queue
+    std::vector<int32_t> order(P->count);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return P->N[a] > P->N[b]; });
+    std::vector<std::vector<int32_t>> qorder;
+    const auto deal = [&](int n) {  // returns the largest queue's items
+        std::vector<int64_t> load(n, 0);
+        qorder.assign(n, {});
+        for (int32_t i : order) {
+            const int qi = int(std::min_element(load.begin(), load.end()) - load.begin());
+            load[qi] += P->N[i];
+            qorder[qi].push_back(i);
+        }
+        return *std::max_element(load.begin(), load.end());
+    };
+    // A queue per XCD keeps a transform's intermediate in that XCD's L2, but
+    // a transform then runs on one XCD alone: where the fullest queue would
+    // hold more than 1.5 times its share (a few large transforms), all XCDs
+    // serve one queue
+    const int kmax = ilog2_pow2(P->N[order[0]]);
+    P->lw = kmax <= kShortMaxLog2 ? kLogST : kmax <= kChipMaxLog2 ? kLogBT : 0;
+    if (P->lw) nx = 1;
+    if (deal(nx) * nx > P->total + P->total / 2 && nx > 1) {
+        nx = 1;
+        deal(nx);
+    }
+    P->coh = nx == 1 && nxcd != 1;  // several XCDs serve one queue
+    P->nq = nx;
+    return qorder;
+}
+
 // Builds jobs, the task order and the device tables of a batch whose
 // per-size plans are fixed.  Returns PACO_OK or an error with the detail set.
 paco_status build_batch(paco_batch_plan_s *P)
@@ -465,39 +505,8 @@ paco_status build_batch(paco_batch_plan_s *P)
     int64_t stw_off[kStageMaxLog2 + 1];
     if (!stage_tables(stw, stw_off)) return bfail(PACO_ERR_INVALID_ARG, "internal: stage twiddle layout mismatch");
 
-    // ---- queues: transforms to XCDs, largest first onto the least loaded ------
-    int nx = queue_count(P->opt);
-    int dev = 0, nxcd = 1;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&nxcd, hipDeviceAttributeNumberOfXccs, dev) != hipSuccess)
-        nxcd = 0;  // unknown: one shared, coherent queue
-    std::vector<int32_t> order(count);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return P->N[a] > P->N[b]; });
-    std::vector<std::vector<int32_t>> qorder;
-    const auto deal = [&](int n) {  // returns the largest queue's items
-        std::vector<int64_t> load(n, 0);
-        qorder.assign(n, {});
-        for (int32_t i : order) {
-            const int qi = int(std::min_element(load.begin(), load.end()) - load.begin());
-            load[qi] += P->N[i];
-            qorder[qi].push_back(i);
-        }
-        return *std::max_element(load.begin(), load.end());
-    };
-    // A queue per XCD keeps a transform's intermediate in that XCD's L2, but
-    // a transform then runs on one XCD alone: where the fullest queue would
-    // hold more than 1.5 times its share (a few large transforms), all XCDs
-    // serve one queue
-    P->lw = ks.back() <= kShortMaxLog2 ? kLogST : ks.back() <= kChipMaxLog2 ? kLogBT : 0;
-    const int lw = P->lw ? P->lw : kLogBT;
-    if (P->lw) nx = 1;
-    if (deal(nx) * nx > P->total + P->total / 2 && nx > 1) {
-        nx = 1;
-        deal(nx);
-    }
-    P->coh = nx == 1 && nxcd != 1;  // several XCDs serve one queue
-    P->nq = nx;
+    const std::vector<std::vector<int32_t>> qorder = deal_queues(P);
+    const int nx = P->nq, lw = P->lw ? P->lw : kLogBT;
     const int resident = P->lw ? resident_small(P->lw) : resident_workgroups(P->coh);
     if (resident <= 0) return bfail(PACO_ERR_HIP, "occupancy query failed");
 
@@ -721,8 +730,12 @@ void free_plan(paco_batch_plan_s *P)
 // ---- autotuner -----------------------------------------------------------------
 // For every transform size of the batch, each candidate split runs a batch of
 // copies of that size (about 2^24 items) through the persistent kernel; the
-// fastest of three timed launches wins.
-paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
+// fastest of three timed launches wins.  Where the batch runs from one shared
+// queue (P->coh: a few large transforms, half-width tiles, coherent stores), so
+// do the trials, with no more copies than the batch has of the size, and eight
+// launches are timed together: nine transforms of 2^18 take 58 us as 1024 x 256
+// and 70 as 512 x 512 there, 256 of them from a queue per XCD 381 and 389.
+paco_status tune(const paco_batch_plan_s *P, std::map<int, SizePlan> &plans, const std::vector<int> &ks)
 {
     bool choice = false;
     for (int k : ks) {
@@ -745,7 +758,9 @@ paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
     }
     for (size_t ki = 0; st == PACO_OK && ki < ks.size(); ++ki) {
         const int k = ks[ki];
-        const int64_t copies = std::min<int64_t>(std::max<int64_t>(1, items >> k), 16384);
+        int64_t copies = std::min<int64_t>(std::max<int64_t>(1, items >> k), 16384);
+        if (P->coh) copies = std::min<int64_t>(copies, std::count(P->N.begin(), P->N.end(), int64_t(1) << k));
+        const int launches = P->coh ? 8 : 1;
         float best = 1e30f;
         const std::vector<SizePlan> cand = paco::candidates(k);
         if (cand.size() == 1) continue;
@@ -759,11 +774,14 @@ paco_status tune(std::map<int, SizePlan> &plans, const std::vector<int> &ks)
             }
             T->total = copies << k;
             T->plans[k] = sp;
+            if (P->coh) T->opt.flags |= PACO_BATCH_ONE_QUEUE;
             st = build_batch(T);
             float ms = 1e30f;
             for (int rep = 0; st == PACO_OK && rep < 4; ++rep) {
-                if ((e = hipEventRecord(e0, s)) != hipSuccess || (e = launch_batch(T, in, out, ws, s)) != hipSuccess ||
-                    (e = hipEventRecord(e1, s)) != hipSuccess || (e = hipEventSynchronize(e1)) != hipSuccess) {
+                e = hipEventRecord(e0, s);
+                for (int i = 0; e == hipSuccess && i < launches; ++i) e = launch_batch(T, in, out, ws, s);
+                if (e != hipSuccess || (e = hipEventRecord(e1, s)) != hipSuccess ||
+                    (e = hipEventSynchronize(e1)) != hipSuccess) {
                     st = bhip(e, "tuning launch");
                     break;
                 }
@@ -802,7 +820,8 @@ bool valid_plan(int k, const SizePlan &sp)
 // reused only on the same architecture and CU count, and only while format
 // stands.  A change of the passes that the candidates are timed on takes a new
 // number, also where the lines look the same (format 1: three phases per
-// transform, whose timings say nothing about the two column passes).
+// transform, whose timings say nothing about the two column passes; format 2:
+// lines without the queue mode).
 std::string cache_key()
 {
     int dev = 0;
@@ -811,13 +830,19 @@ std::string cache_key()
     std::string arch = prop.gcnArchName;
     for (char &ch : arch)
         if (ch == ' ') ch = '_';
-    return arch + " cus=" + std::to_string(prop.multiProcessorCount) + " format=2";
+    return arch + " cus=" + std::to_string(prop.multiProcessorCount) + " format=3";
 }
 
-// Tuning cache: a "key <device key>" line, then lines "log2N l1 l2 t";
+// The entries of a tuning cache: by log2 N and by the queue mode they were
+// timed in (1: one shared queue; always 0 up to 2^14 items, where there is no
+// choice).
+typedef std::map<std::pair<int, int>, SizePlan> CacheLines;
+std::pair<int, int> cache_entry(int k, bool shared) { return {k, k > paco::kChipMaxLog2 && shared ? 1 : 0}; }
+
+// Tuning cache: a "key <device key>" line, then lines "log2N l1 l2 t shared";
 // '#' starts a comment.  A file with another key (or none) is ignored, and
 // rewritten after tuning.
-void read_cache(const char *path, const std::string &key, std::map<int, SizePlan> &plans)
+void read_cache(const char *path, const std::string &key, CacheLines &plans)
 {
     std::ifstream f(path);
     std::string line;
@@ -830,21 +855,24 @@ void read_cache(const char *path, const std::string &key, std::map<int, SizePlan
         }
         if (!keyed) continue;
         std::istringstream is(line);
-        int k;
+        int k, shared;
         SizePlan sp;
-        if (is >> k >> sp.l1 >> sp.l2 >> sp.t)
-            if (k >= paco::kBatchMinLog2 && k <= paco::kBatchMaxLog2 && valid_plan(k, sp)) plans[k] = sp;
+        if (is >> k >> sp.l1 >> sp.l2 >> sp.t >> shared)
+            if (k >= paco::kBatchMinLog2 && k <= paco::kBatchMaxLog2 && valid_plan(k, sp) &&
+                (shared == 0 || shared == 1))
+                plans[cache_entry(k, shared == 1)] = sp;
     }
 }
 
-bool write_cache(const char *path, const std::string &key, const std::map<int, SizePlan> &plans)
+bool write_cache(const char *path, const std::string &key, const CacheLines &plans)
 {
     std::ofstream f(path);
     if (!f) return false;
-    f << "# paco batched plan cache: log2N l1 l2 t (N1 = 2^l1, N2 = 2^l2, b = 2^t)\n";
+    f << "# paco batched plan cache: log2N l1 l2 t shared (N1 = 2^l1, N2 = 2^l2, b = 2^t; shared: one work queue)\n";
     f << "key " << key << '\n';
     for (auto &kv : plans)
-        f << kv.first << ' ' << kv.second.l1 << ' ' << kv.second.l2 << ' ' << kv.second.t << '\n';
+        f << kv.first.first << ' ' << kv.second.l1 << ' ' << kv.second.l2 << ' ' << kv.second.t << ' '
+          << kv.first.second << '\n';
     return bool(f);
 }
 
@@ -900,27 +928,31 @@ paco_status paco_batch_plan_create_ex(paco_batch_plan **bp, int32_t count, const
         free_plan(P);
         return bhip(e, "hipGetDevice");
     }
-    // per-size plans: cache file, then tuning (unless PACO_BATCH_NO_TUNE), else defaults
-    std::map<int, SizePlan> plans;
+    // per-size plans: cache file (lines of this batch's queue mode), then tuning
+    // (unless PACO_BATCH_NO_TUNE), else defaults
+    (void)deal_queues(P);
+    CacheLines lines;
     const std::string key = cache_key();
-    if (tune_cache_path) read_cache(tune_cache_path, key, plans);
+    if (tune_cache_path) read_cache(tune_cache_path, key, lines);
     std::vector<int> missing;
-    for (int k : ks)
-        if (!plans.count(k)) missing.push_back(k);
-    const bool tuning = !(opt.flags & PACO_BATCH_NO_TUNE);
-    if (!missing.empty() && tuning) {
-        paco_status st = tune(plans, missing);
+    for (int k : ks) {
+        const auto at = lines.find(cache_entry(k, P->coh));
+        if (at == lines.end()) missing.push_back(k);
+        else P->plans[k] = at->second;
+    }
+    if (!missing.empty() && !(opt.flags & PACO_BATCH_NO_TUNE)) {
+        paco_status st = tune(P, P->plans, missing);
         if (st != PACO_OK) {
             free_plan(P);
             return st;
         }
-    }
-    for (int k : ks)
-        if (!plans.count(k)) plans[k] = paco::candidates(k).front();
-    for (int k : ks) P->plans[k] = plans[k];
-    if (tune_cache_path && !missing.empty() && tuning && !write_cache(tune_cache_path, key, plans)) {
-        free_plan(P);
-        return bfail(PACO_ERR_INVALID_ARG, std::string("cannot write the tuning cache ") + tune_cache_path);
+        for (int k : missing) lines[cache_entry(k, P->coh)] = P->plans[k];
+        if (tune_cache_path && !write_cache(tune_cache_path, key, lines)) {
+            free_plan(P);
+            return bfail(PACO_ERR_INVALID_ARG, std::string("cannot write the tuning cache ") + tune_cache_path);
+        }
+    } else {
+        for (int k : missing) P->plans[k] = paco::candidates(k).front();
     }
     paco_status st = build_batch(P);
     if (st != PACO_OK) {

@@ -48,6 +48,37 @@ def test_file_of_another_format_is_ignored_and_rewritten(tmp_path, key):
     assert [ln.split()[0] for ln in lines] == ["17"] and len(lines[0].split()) < 6, lines
 
 
+def _lines(path):
+    return sorted(ln.split() for ln in open(path).read().splitlines() if ln and not ln.startswith(("#", "key ")))
+
+
+def test_lines_hold_for_the_queue_mode_they_were_timed_in(tmp_path, key):
+    path = str(tmp_path / "tune.txt")
+    few, many = [1 << 18], [1 << 18] * 64
+    for lines, want_few, want_many in ((["18 10 8 1 0"], 512, 1024), (["18 10 8 1 1"], 1024, 512),
+                                       (["18 10 8 1 1", "18 8 10 1 0"], 1024, 256)):
+        with open(path, "w") as f:
+            f.write("\n".join([key] + lines) + "\n")
+        for sizes, flags, mode, want in ((few, 0, "shared queue", want_few), (many, 0, "one per XCD", want_many),
+                                         (many, paco.PACO_BATCH_ONE_QUEUE, "shared queue", want_few)):
+            plan = paco.BatchPlan(sizes, tune_cache_path=path, flags=NO_TUNE | flags)
+            assert mode in plan.description and plan.transform_plan(0)[0] == want, (lines, mode)
+
+
+def test_tuning_runs_in_the_batchs_queue_mode(tmp_path, key):
+    path = str(tmp_path / "tune.txt")
+    shared = paco.BatchPlan([1 << 18, 1 << 17, 1 << 10], tune_cache_path=path)
+    assert "shared queue" in shared.description
+    first = _lines(path)
+    assert [(ln[0], ln[4]) for ln in first] == [("10", "0"), ("17", "1"), ("18", "1")]
+    many = paco.BatchPlan([1 << 18] * 64 + [1 << 10], tune_cache_path=path)   # 2^18 is tuned anew
+    assert "one per XCD" in many.description
+    both = _lines(path)
+    assert [(ln[0], ln[4]) for ln in both] == [("10", "0"), ("17", "1"), ("18", "0"), ("18", "1")]
+    assert all(ln in both for ln in first)
+    assert _key(path) == key
+
+
 def _stream() -> int:
     return torch.cuda.current_stream().cuda_stream
 
@@ -67,7 +98,7 @@ SPLITS = [(7, 8), (8, 7), (8, 8), (8, 9), (9, 8), (8, 10), (9, 9), (10, 8), (9, 
 def test_every_choice_of_the_tuner_has_the_single_plans_bits(tmp_path, key, l1, l2, flags):
     path = str(tmp_path / "tune.txt")
     with open(path, "w") as f:
-        f.write(f"{key}\n{l1 + l2} {l1} {l2} 1\n")
+        f.write(f"{key}\n{l1 + l2} {l1} {l2} 1 {int(bool(flags))}\n")
     plan = paco.BatchPlan([1 << (l1 + l2)] * 16, tune_cache_path=path, flags=NO_TUNE | flags)
     assert plan.transform_plan(0)[:2] == (1 << l1, 1 << l2)
     assert ("shared queue" if flags else "one per XCD") in plan.description
@@ -100,7 +131,7 @@ def test_tuned_batch_has_the_single_plans_bits(tmp_path):
 def test_other_splits_are_no_choice(tmp_path, key, k, l1):
     path = str(tmp_path / "tune.txt")
     with open(path, "w") as f:
-        f.write(f"{key}\n{k} {l1} {k - l1} 1\n")
+        f.write(f"{key}\n{k} {l1} {k - l1} 1 0\n")
     plan = paco.BatchPlan([1 << k] * 16, tune_cache_path=path, flags=NO_TUNE)
     assert plan.transform_plan(0)[0] == 1 << (k + 1) // 2
     # the single plan of that shape runs the balanced split
