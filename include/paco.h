@@ -225,12 +225,17 @@ paco_status paco_plan_workspace_size(const paco_plan *plan, size_t *bytes);
  *   N >= 2^24: a shape without a symmetric form runs the passes of
  *     2^floor(l/2) x 2^ceil(l/2), at 2^28 of 8192 x 32768, and so does
  *     16384 x 16384.
- * b and p never enter the result, N1 and N2 only as said above.  The split MFMA forms run two
- * column passes of their own lengths with N1 and N2 both in [2^7, 2^11].  The
- * stage hooks of paco_execute_stage run the phases (or the split or symmetric
- * passes) of the plan's own shape in every case; where paco_execute runs
- * another split the two agree within rounding.  paco_plan_describe names what
- * runs ("direct[...]", "executes ...") and counts its launches. */
+ * b and p never enter the result, N1 and N2 only as said above.  The split MFMA
+ * forms run two column passes of their own lengths with N1 and N2 both in
+ * [2^7, 2^11].  paco_plan_describe names what runs ("direct[...]", "executes
+ * ...") and counts its launches.
+ *
+ * The stage hooks of paco_execute_stage run the passes of the plan's own shape
+ * in every case.  One rule says when those are the passes of paco_execute, bit
+ * for bit: exactly when the description holds neither " direct[" nor
+ * "executes".  Otherwise the two agree within rounding.  An option that asks
+ * for a form (PACO_PLAN_NO_SYM, for one) keeps paco_execute on the plan's own
+ * passes. */
 paco_status paco_execute(const paco_plan *plan, const void *in, void *out, void *workspace,
                          size_t workspace_bytes, void *stream);
 
