@@ -386,10 +386,11 @@ paco_status bfail(paco_status st, const std::string &msg)
     return st;
 }
 
-paco_status bhip(hipError_t e, const char *what)
+// (the runtime's last error is taken back: see hip_fail in plan.hip)
+paco_status bhip(hipError_t e, const char *what, paco_status st = PACO_ERR_HIP)
 {
-    paco::set_last_error(std::string(what) + ": " + hipGetErrorString(e));
-    return PACO_ERR_HIP;
+    (void)hipGetLastError();
+    return bfail(st, std::string(what) + ": " + hipGetErrorString(e));
 }
 
 const void *kernel_of(bool coh)
@@ -646,7 +647,7 @@ paco_status build_batch(paco_batch_plan_s *P)
     hipError_t e = hipMalloc(&P->dev, total);
     if (e != hipSuccess) {
         P->dev = nullptr;
-        return bfail(PACO_ERR_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e));
+        return bhip(e, "hipMalloc", PACO_ERR_ALLOC);
     }
     auto at = [&](size_t i) { return static_cast<unsigned char *>(P->dev) + pieces[i].off; };
     for (size_t s = 0; s < his.size(); ++s) {
@@ -747,7 +748,7 @@ paco_status tune(const paco_batch_plan_s *P, std::map<int, SizePlan> &plans, con
     const int64_t items = int64_t(1) << 24;
     void *buf = nullptr;
     hipError_t e = hipMalloc(&buf, size_t(items) * 8 * 3);
-    if (e != hipSuccess) return bfail(PACO_ERR_ALLOC, std::string("tuning buffers: ") + hipGetErrorString(e));
+    if (e != hipSuccess) return bhip(e, "tuning buffers", PACO_ERR_ALLOC);
     float2 *in = static_cast<float2 *>(buf), *out = in + items, *ws = out + items;
     hipStream_t s = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -33,10 +33,13 @@ paco_status fail(paco_status st, const std::string &msg)
     return st;
 }
 
-paco_status hip_fail(hipError_t e, const char *what)
+// A runtime error that a status reports, or that the library copes with, is
+// taken back from the runtime: its thread's last error stays until it is read,
+// and the next launch that checks it, here or in another library, would fail.
+paco_status hip_fail(hipError_t e, const char *what, paco_status st = PACO_ERR_HIP)
 {
-    g_last_error = std::string(what) + ": " + hipGetErrorString(e);
-    return PACO_ERR_HIP;
+    (void)hipGetLastError();
+    return fail(st, std::string(what) + ": " + hipGetErrorString(e));
 }
 
 int ilog2_exact(int64_t n)
@@ -67,6 +70,7 @@ void *scratch_for_device(int dev, std::string &err)
         void *ptr = nullptr;
         const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
         if (e != hipSuccess || !ptr) {
+            (void)hipGetLastError();
             err = std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e);
             return nullptr;
         }
@@ -339,7 +343,7 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
     // cannot have it still works through the other entry points)
     P->scratch = scratch_for_device(P->device, P->scratch_error);
     e = hipMalloc(&P->dev_tables, total);
-    if (e != hipSuccess) { P->dev_tables = nullptr; delete P; return fail(PACO_ERR_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e)); }
+    if (e != hipSuccess) { delete P; return hip_fail(e, "hipMalloc", PACO_ERR_ALLOC); }
     std::vector<unsigned char> staging(total, 0);
     for (auto &pc : pieces)
         if (pc.bytes) std::memcpy(staging.data() + pc.off, pc.src, pc.bytes);
