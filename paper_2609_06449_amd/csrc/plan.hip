@@ -705,8 +705,12 @@ paco_status create_with_inverse(paco_plan **plan, int64_t N1, int64_t N2, int64_
         if (create_impl(&best, int64_t(1) << best1, int64_t(1) << (lN - best1), 2, 2, dt, o) != PACO_OK) best = nullptr;
         g_last_error = note;
         if (best) {
-            if (!(*plan)->sym || N1 == N2) (*plan)->fwd = best;  // and the inverse
-            else (*plan)->inv = best;
+            if (!(*plan)->sym || N1 == N2) {  // and the inverse
+                (*plan)->fwd = best;
+                (*plan)->desc += " | executes " + best->desc;
+            } else {
+                (*plan)->inv = best;
+            }
             return PACO_OK;
         }
     }
@@ -766,8 +770,7 @@ paco_status paco_plan_describe(const paco_plan *plan, int32_t *launches, char *b
                     : plan->sym    ? 3
                                    : int32_t((plan->split ? 2 : plan->phase1.size() + 1) + plan->phase3.size());
     if (buf && buflen) {
-        const std::string d = plan->fwd ? plan->desc + " | executes " + plan->fwd->desc : plan->desc;
-        std::strncpy(buf, d.c_str(), buflen - 1);
+        std::strncpy(buf, plan->desc.c_str(), buflen - 1);
         buf[buflen - 1] = 0;
     }
     return PACO_OK;
