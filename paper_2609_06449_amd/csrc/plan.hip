@@ -315,7 +315,7 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
         } else {
             P->direct_form = paco::direct_form(P->l1, P->l2);
         }
-        if (P->direct_form.l1) {
+        if (P->direct_form.l1 && !(two_pass_tables && P->direct_form.l1 == P->l1)) {  // (else tcw is that table)
             const int64_t n = int64_t(16) << P->direct_form.l1;
             tdw.resize(size_t(n));
             for (int64_t k = 0; k < n; ++k) tdw[k] = paco::root_neg(k, n);
@@ -366,7 +366,7 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
         f.hi = d_thi;
         f.lo = d_tlo;
         f.log2Lo = P->lLo;
-        f.cw = reinterpret_cast<const float2 *>(at(8));
+        f.cw = reinterpret_cast<const float2 *>(at(tdw.empty() ? 5 : 8));
     }
 
     auto base_pass = [&](int64_t ld, int64_t ncols, int log2n) {

@@ -12,14 +12,16 @@ enum { ok = 0, invalid_value = 1, out_of_memory = 2 };
 
 static hipError_t last;
 static int mallocs, frees, launches;
+static uint64_t bytes;
 static uint64_t fail_mask; /* bit i: the i-th hipMalloc from now fails */
 static dim3 grid_, block_;
 static size_t shared_;
 static void *stream_;
 static char symbol_[256];
 
-void stub_fail_mallocs(uint64_t mask) { mallocs = frees = launches = 0; fail_mask = mask; }
+void stub_fail_mallocs(uint64_t mask) { mallocs = frees = launches = 0; bytes = 0; fail_mask = mask; }
 int stub_mallocs(void) { return mallocs; }
+uint64_t stub_bytes(void) { return bytes; } /* asked for in all */
 int stub_frees(void) { return frees; }
 int stub_launches(void) { return launches; }
 
@@ -31,6 +33,7 @@ const char *hipGetErrorString(hipError_t e) { return e == ok ? "no error" : e ==
 hipError_t hipMalloc(void **p, size_t n)
 {
     const int i = mallocs++;
+    bytes += n;
     *p = i < 64 && (fail_mask >> i & 1) ? NULL : aligned_alloc(256, (n + 255) & ~(size_t)255);
     if (*p) return ok;
     ++frees; /* nothing to free */

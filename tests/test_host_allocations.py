@@ -1,6 +1,6 @@
-"""Host code under failed device allocations, on the CPU: the library is loaded
-against a stub of the HIP runtime (tests/stub/hip_stub.c) in a process of its
-own, which fails the allocations that a case names."""
+"""The library's host code and its device allocations, on the CPU: the library is
+loaded against a stub of the HIP runtime (tests/stub/hip_stub.c) in a process of
+its own, which counts allocations and fails those that a case names."""
 import os
 import shutil
 import subprocess
@@ -78,8 +78,29 @@ for make in (lambda: paco.Plan(64, 64, 4, 4), lambda: paco.Plan(1 << 14, 1 << 14
 print("ok")
 """
 
+TABLES = r"""
+import ctypes, sys
+hip = ctypes.CDLL(sys.argv[1])
+hip.stub_bytes.restype = ctypes.c_uint64
+hip.stub_fail_mallocs.argtypes = [ctypes.c_uint64]
+from paper_2609_06449_amd import paco
 
-def test_failed_allocations_leave_no_error_and_no_memory_behind(tmp_path):
+
+def tables(shape, **kw):
+    hip.stub_fail_mallocs(0)
+    p = paco.Plan(*shape, 2, 2, **kw)
+    return p.description, hip.stub_bytes()
+
+
+for shape in ((256, 256), (1024, 512), (1024, 1024), (2048, 1024), (2048, 2048)):
+    (direct, a), (phases, b) = tables(shape), tables(shape, flags=paco.PACO_PLAN_NO_SPLIT)
+    assert " direct[two column passes, " in direct and " direct[" not in phases
+    assert a == b if shape[0] == shape[1] else a < b, (shape, a, b)  # (b: with the swapped shape's for the inverse)
+print("ok")
+"""
+
+
+def _on_the_stub(tmp_path, script):
     cc = shutil.which("gcc") or shutil.which("cc")
     if cc is None:
         pytest.skip("no C compiler")
@@ -88,5 +109,14 @@ def test_failed_allocations_leave_no_error_and_no_memory_behind(tmp_path):
                     "-Wl,-soname,libamdhip64.so.7"], check=True)
     assert paco.lib() is not None
     env = dict(os.environ, LD_LIBRARY_PATH=str(tmp_path))
-    r = subprocess.run([sys.executable, "-c", SCRIPT, stub], cwd=ROOT, env=env, capture_output=True, text=True, timeout=120)
+    r = subprocess.run([sys.executable, "-c", script, stub], cwd=ROOT, env=env, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+def test_failed_allocations_leave_no_error_and_no_memory_behind(tmp_path):
+    _on_the_stub(tmp_path, SCRIPT)
+
+
+def test_column_passes_take_no_second_table(tmp_path):
+    # w_{16 N1}^{-k} is the two-pass form's table as well
+    _on_the_stub(tmp_path, TABLES)
