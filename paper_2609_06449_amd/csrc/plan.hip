@@ -211,8 +211,10 @@ namespace {
 
 // Builds the passes and tables of one factorisation N1 x N2 (the forward
 // transform's; paco_plan_create builds a second, N2 x N1, for the inverse).
+// sym_only: a shape with the symmetric form of which only that form will run
+// (no stage hooks, no two-pass form): without the tables of the others.
 paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int32_t b, paco_dtype dt,
-                        const paco_plan_options &opt)
+                        const paco_plan_options &opt, bool sym_only = false)
 {
     if (!plan) return fail(PACO_ERR_INVALID_ARG, "plan out-pointer is NULL");
     *plan = nullptr;
@@ -259,12 +261,13 @@ paco_status create_impl(paco_plan **plan, int64_t N1, int64_t N2, int64_t p, int
     for (int64_t r = 0; r < L; ++r) tw[r] = paco::root_neg(r, L);
     // the two-pass form's column factor w_{16 N1}^{-k} (single-pass Phase III
     // over at most 2^12 columns: a table of at most 512 KiB)
-    const bool two_pass_tables = dt == PACO_C64 && P->l2 <= paco::kMaxOnChipLog2 && P->l1 <= 12;
+    const bool two_pass_tables = !sym_only && dt == PACO_C64 && P->l2 <= paco::kMaxOnChipLog2 && P->l1 <= 12;
     if (two_pass_tables) {
         tcw.resize(size_t(16 * N1));
         for (int64_t k = 0; k < 16 * N1; ++k) tcw[k] = paco::root_neg(k, 16 * N1);
     }
-    paco::middle_tables(P->lN, thi, tlo, ttile);
+    if (sym_only) paco::top_tables(P->lN, thi, tlo);
+    else paco::middle_tables(P->lN, thi, tlo, ttile);
     // the symmetric split form (N1 = 16 L1, N2 = 16 L2; option
     // PACO_PLAN_NO_SYM): square shapes with L = 256 and 512 for every dtype,
     // 1024 in FP32; in FP32 also every non-square pair of N1, N2 in {2^12,
@@ -702,7 +705,7 @@ paco_status create_with_inverse(paco_plan **plan, int64_t N1, int64_t N2, int64_
         if ((*plan)->l1 == best1) return PACO_OK;  // the inverse runs its own passes
         paco_plan *best = nullptr;
         paco_plan_options o{};
-        if (create_impl(&best, int64_t(1) << best1, int64_t(1) << (lN - best1), 2, 2, dt, o) != PACO_OK) best = nullptr;
+        if (create_impl(&best, int64_t(1) << best1, int64_t(1) << (lN - best1), 2, 2, dt, o, true) != PACO_OK) best = nullptr;
         g_last_error = note;
         if (best) {
             if (!(*plan)->sym || N1 == N2) {  // and the inverse

@@ -12,7 +12,7 @@ enum { ok = 0, invalid_value = 1, out_of_memory = 2 };
 
 static hipError_t last;
 static int mallocs, frees, launches;
-static uint64_t bytes;
+static uint64_t bytes, sizes[64];
 static uint64_t fail_mask; /* bit i: the i-th hipMalloc from now fails */
 static dim3 grid_, block_;
 static size_t shared_;
@@ -22,6 +22,7 @@ static char symbol_[256];
 void stub_fail_mallocs(uint64_t mask) { mallocs = frees = launches = 0; bytes = 0; fail_mask = mask; }
 int stub_mallocs(void) { return mallocs; }
 uint64_t stub_bytes(void) { return bytes; } /* asked for in all */
+uint64_t stub_size(int i) { return sizes[i]; } /* by the i-th hipMalloc */
 int stub_frees(void) { return frees; }
 int stub_launches(void) { return launches; }
 
@@ -34,6 +35,7 @@ hipError_t hipMalloc(void **p, size_t n)
 {
     const int i = mallocs++;
     bytes += n;
+    if (i < 64) sizes[i] = n;
     *p = i < 64 && (fail_mask >> i & 1) ? NULL : aligned_alloc(256, (n + 255) & ~(size_t)255);
     if (*p) return ok;
     ++frees; /* nothing to free */

@@ -96,6 +96,14 @@ for shape in ((256, 256), (1024, 512), (1024, 1024), (2048, 1024), (2048, 2048))
     (direct, a), (phases, b) = tables(shape), tables(shape, flags=paco.PACO_PLAN_NO_SPLIT)
     assert " direct[two column passes, " in direct and " direct[" not in phases
     assert a == b if shape[0] == shape[1] else a < b, (shape, a, b)  # (b: with the swapped shape's for the inverse)
+
+# the balanced shape behind a plan: its symmetric passes only, not the tables of
+# Phase II's hook (128 x 128) and of the two-pass form (16 x 4096)
+hip.stub_size.restype = ctypes.c_uint64
+assert "executes sym[" in tables((1 << 10, 1 << 14))[0]
+second = hip.stub_size(1)
+assert "executes" not in tables((1 << 12, 1 << 12))[0]
+assert second == hip.stub_size(0) - 8 * (128 * 128 + 16 * 4096), (second, hip.stub_size(0))
 print("ok")
 """
 
