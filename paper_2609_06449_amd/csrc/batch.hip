@@ -48,7 +48,6 @@ constexpr int kBT = 512;             // threads per workgroup of the persistent 
 constexpr int kBatchMinLog2 = 2;     // N >= 4 (N1, N2 >= 2)
 constexpr int kBatchMaxLog2 = 20;    // pass lengths <= 2^10
 constexpr int kChipMaxLog2 = kDirectChipLog2;  // whole transform inside one workgroup
-constexpr int kTileLog2 = 14;        // items of a pass tile: 32 per thread, in two groups
 constexpr int kPassMin = 7, kPassMax = kBatchPassMax;
 constexpr uint32_t kSpinLimit = 1u << 22;
 // s_waitcnt operand that waits for vmcnt = 0 only (gfx9 encoding: vmcnt in
@@ -107,14 +106,6 @@ struct BatchArgs {
 // (kept live across the others, it spilled).
 __device__ __forceinline__ int own(int tid) { return int(opaque(uint32_t(tid))); }
 
-// Columns (log2) of a pass tile of 2^l points.  The shared queue serves few
-// large transforms, which a full tile leaves on too few workgroups: half a
-// tile there, 16 items per thread in one group (one transform of 2^16 32 -> 22
-// us, of 2^20 35 -> 30, nine of 2^20 117 -> 95).
-constexpr int pass_lt(int l, bool coh) { return (coh ? kTileLog2 - 1 : kTileLog2) - l; }
-// transforms of 2^l points a small task of 2^lw threads holds: 16 items per
-// thread (shorter ones: one transform per thread)
-constexpr int small_lt(int l, int lw) { return l < 4 ? lw : lw + 4 - l; }
 constexpr int kLogBT = 9;      // the persistent kernel's threads
 static_assert(kBT == 1 << kLogBT, "threads per workgroup");
 // Batches without a transform of two passes need no work queue: a plain

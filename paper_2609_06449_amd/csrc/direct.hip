@@ -41,7 +41,7 @@ DirectForm direct_form(int l1, int l2)
     DirectForm f{};
     f.log2N = l1 + l2;
     if (f.log2N <= kDirectChipLog2) return f;
-    f.l1 = batch_split(l1, l2) ? l1 : (f.log2N + 1) / 2;
+    f.l1 = direct_l1(l1, l2);
     f.l2 = f.log2N - f.l1;
     return f;
 }

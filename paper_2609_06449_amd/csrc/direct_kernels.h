@@ -21,46 +21,30 @@ hipError_t direct_pass_mf(int prec, bool b, int l, int lcols, const DirectArgs &
 
 namespace {
 
-// Tiles of 4 columns: 32-byte runs of x and of y, which the tiles beside it on
-// the same XCD (tile_order) complete to lines in its L2.  What bounds a pass
-// here is its launch and one chain of load, arithmetic, store per workgroup,
-// so the most workgroups win: 4 columns against 8 in both passes took 11.2
-// against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
-// 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
-constexpr int kLT = 2;
-// 4096-point columns (pass A of 2^23 only): 8 columns in two LDS groups, 1024
-// threads and 136 KiB, whose 64-byte runs are read last-use (pass_a_tile).
-// 2^23: 72 us, with 4 columns and two workgroups per CU 79; the three-pass forms
-// it replaces took 95 to 130 by shape.  2^24 in two passes of 4 columns took 191
-// us against 162 (now 132) for the symmetric form's three, which ends the range.
-constexpr int groups(int l) { return l == 12 ? 2 : 1; }
-// (the split MFMA forms' butterflies need full waves: 8 columns of 128 points)
-__host__ __device__ constexpr int tile_cols(int l, int prec) { return l == 12 || (prec != kPrecFP32 && l == 7) ? 3 : kLT; }
-
 template <int L, int PREC>
-__global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC), groups(L))) void direct_a_kernel(DirectArgs P)
+__global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC != kPrecFP32), tile_groups(L))) void direct_a_kernel(DirectArgs P)
 {
-    constexpr int LT = tile_cols(L, PREC);
-    __shared__ float2 smem[tile_lds(L, LT, groups(L))];
-    pass_a_tile<L, LT, groups(L), false, PREC>(P.src, P.dst, P.l2, tile_cols(P.l2, PREC),
+    constexpr int LT = tile_cols(L, PREC != kPrecFP32);
+    __shared__ float2 smem[tile_lds(L, LT, tile_groups(L))];
+    pass_a_tile<L, LT, tile_groups(L), false, PREC>(P.src, P.dst, P.l2, tile_cols(P.l2, PREC != kPrecFP32),
                                                uint32_t(tile_order(blockIdx.x, gridDim.x)) << LT, P.stw, smem,
                                                threadIdx.x, P.conj_in != 0);
 }
 
 template <int L, int PREC>
-__global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC), groups(L))) void direct_b_kernel(DirectArgs P)
+__global__ __launch_bounds__(tile_threads(L, tile_cols(L, PREC != kPrecFP32), tile_groups(L))) void direct_b_kernel(DirectArgs P)
 {
-    constexpr int LT = tile_cols(L, PREC);
-    __shared__ float2 smem[tile_lds(L, LT, groups(L))];
-    pass_b_tile<L, LT, groups(L), PREC>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << LT, P.top,
+    constexpr int LT = tile_cols(L, PREC != kPrecFP32);
+    __shared__ float2 smem[tile_lds(L, LT, tile_groups(L))];
+    pass_b_tile<L, LT, tile_groups(L), PREC>(P.src, P.dst, P.l1, uint32_t(tile_order(blockIdx.x, gridDim.x)) << LT, P.top,
                                         P.stw, smem, threadIdx.x, P.out_scale);
 }
 
 template <int L, int PREC>
 void launch_pass(bool b, int lcols, const DirectArgs &a, hipStream_t s)
 {
-    constexpr int LT = tile_cols(L, PREC);
-    const dim3 tiles(1u << (lcols - LT)), threads(tile_threads(L, LT, groups(L)));
+    constexpr int LT = tile_cols(L, PREC != kPrecFP32);
+    const dim3 tiles(1u << (lcols - LT)), threads(tile_threads(L, LT, tile_groups(L)));
     if constexpr (L < 12) {  // 4096 points: pass A only
         if (b) {
             hipLaunchKernelGGL((direct_b_kernel<L, PREC>), tiles, threads, 0, s, a);

@@ -7,7 +7,7 @@
 #include <string>
 #include <vector>
 
-#include "addr.h"
+#include "tile_addr.h"
 
 namespace paco {
 
@@ -24,45 +24,6 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 constexpr int kMaxOnChipLog2 = 12;
 // Largest length the stage tables cover (tiles of the direct form, tile.h).
 constexpr int kStageMaxLog2 = 13;
-
-// ---------------------------------------------------------------------------
-// Stage plan of an on-chip transform of length n = 2^l: radix-16 Stockham
-// stages, then one radix-2^(l mod 4) stage when l is not a multiple of 4.
-// ---------------------------------------------------------------------------
-__host__ __device__ constexpr int stage_count(int l) { return l / 4 + (l % 4 ? 1 : 0); }
-__host__ __device__ constexpr int stage_log2radix(int l, int s) { return s < l / 4 ? 4 : l % 4; }
-__host__ __device__ constexpr int stage_log2ns(int l, int s)
-{
-    int a = 0;
-    for (int i = 0; i < s; ++i) a += stage_log2radix(l, i);
-    return a;
-}
-
-// Stage twiddles w_M^{-k r} (M = Ns*R, k < Ns, 1 <= r < R) are stored as two
-// factor tables per stage S >= 1, indexed (r-1, .):
-//   lo[r-1][kl] = w_M^{-kl*r},       kl < min(Ns, 16)
-//   hi[r-1][kh] = w_M^{-16*kh*r},    kh < Ns/16        (only when Ns > 16)
-// with k = 16*kh + kl, so w_M^{-k r} = hi * lo.  Lanes of a wave hold
-// consecutive k, so every table read is a broadcast or a contiguous run.
-__host__ __device__ constexpr int stage_lo_width(int l, int s)
-{
-    return (1 << stage_log2ns(l, s)) < 16 ? (1 << stage_log2ns(l, s)) : 16;
-}
-__host__ __device__ constexpr int stage_hi_width(int l, int s)
-{
-    return (1 << stage_log2ns(l, s)) > 16 ? (1 << stage_log2ns(l, s)) / 16 : 0;
-}
-__host__ __device__ constexpr int stage_tw_size(int l, int s)
-{
-    return s == 0 ? 0 : ((1 << stage_log2radix(l, s)) - 1) * (stage_lo_width(l, s) + stage_hi_width(l, s));
-}
-__host__ __device__ constexpr int stage_tw_offset(int l, int s)
-{
-    int a = 0;
-    for (int i = 1; i < s; ++i) a += stage_tw_size(l, i);
-    return a;
-}
-__host__ __device__ constexpr int stage_tw_total(int l) { return stage_tw_offset(l, stage_count(l)); }
 
 // Tile width of the fast kernels: 4096 items per workgroup for short
 // transforms, 4 columns (32-byte row runs) for long ones.
@@ -214,21 +175,6 @@ struct SymPass {
 // picked.  Otherwise neither N1 x N2 nor b nor p of the plan enters the result.
 // The split MFMA forms run the two passes too, of the lengths N1 and N2 of the
 // plan (2^7 .. 2^11 each).
-constexpr int kDirectChipLog2 = 14;  // the largest transform of one workgroup
-constexpr int kDirectMaxLog2 = 23;
-constexpr int kBatchPassMax = 10;    // pass lengths of the batched kernel: up to 2^10
-// The splits of N = 2^15 .. 2^20 that the batched form's tuner chooses from.
-// Passes of 2^8 .. 2^10 points, 2^7 only at 2^15, where every split has one: a
-// single plan's 4-column tile of 128 points is half a wave.  us per call as
-// balanced / as N1 x N2: 256 x 1024 10.6 / 10.5, 1024 x 256 10.6 / 10.7, 512 x 1024 12.6 /
-// 12.0, 128 x 256 8.8 / 8.9, all within a run's noise; but 512 x 128 8.8 / 9.0 and
-// 1024 x 128 9.0 / 9.9, for which a large batch gave nothing back (512 of 2^17
-// 384 / 386 us, 1024 of 2^16 374 / 369).
-constexpr bool batch_split(int l1, int l2)
-{
-    return l1 + l2 > kDirectChipLog2 && l1 <= kBatchPassMax && l2 <= kBatchPassMax &&
-           ((l1 >= 8 && l2 >= 8) || (l1 + l2 == 15 && l1 >= 7 && l2 >= 7));
-}
 struct DirectForm {
     int32_t log2N, l1, l2;           // two passes: pass A 2^l1 points over 2^l2 columns, pass B the reverse (else 0)
     int32_t prec;                    // radix-16 butterflies of the two passes (paco_dtype)

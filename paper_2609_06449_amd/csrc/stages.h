@@ -132,9 +132,6 @@ __device__ __forceinline__ void st2(char *p, float2 v)
         *reinterpret_cast<float2 *>(p) = v;
     }
 }
-// LDS index with 4 pad items per 64: the radix-16 first-stage writes (row
-// stride 16*T items) land on distinct banks.
-__device__ __forceinline__ int lpad(int e) { return e + ((e >> 6) << 2); }
 
 struct Ctx {
     float2 *lds;

@@ -28,43 +28,6 @@
 namespace paco {
 namespace {
 
-__host__ __device__ constexpr int tile_items(int l) { return l < 4 ? 1 << l : 16; }
-// threads of a tile of 2^lt columns in h groups
-__host__ __device__ constexpr int tile_threads(int l, int lt, int h) { return (1 << (l + lt)) / (h * tile_items(l)); }
-__host__ __device__ constexpr int tile_tw(int l) { return (stage_tw_total(l) + 31) & ~31; }
-// items of LDS: the stage twiddles and one group's exchange buffer with its
-// padding (one item per 16 in both orders; transforms of at most 16 points
-// exchange nothing)
-__host__ __device__ constexpr int tile_lds(int l, int lt, int h)
-{
-    const int g = (1 << (l + lt)) / h;
-    return tile_tw(l) + (l > 4 || lt > 0 ? g + (g >> 4) + 4 : 4);
-}
-
-// Place of (row, column t) in the exchange buffer.  Column fastest: lpad.
-// Index fastest: one pad item per 16, which puts the stride-16 stores of a
-// radix-16 stage on distinct banks.
-template <int L, int LTG, bool JF>
-__device__ __forceinline__ int tile_slot(int row, int t)
-{
-    if constexpr (JF) {
-        const int i = (t << L) + row;
-        return i + (i >> 4);
-    } else {
-        return lpad((row << LTG) + t);
-    }
-}
-template <int LTG, int LJ, bool JF>
-__device__ __forceinline__ int tile_col(int g)
-{
-    return JF ? g >> LJ : g & ((1 << LTG) - 1);
-}
-template <int LTG, int LJ, bool JF>
-__device__ __forceinline__ int tile_idx(int g)
-{
-    return JF ? g & ((1 << LJ) - 1) : g >> LTG;
-}
-
 // Stages S.. of a tile: v holds the operands of stage S (v[h E + i R + r]:
 // operand r of butterfly g = tid + i NT of group h); store(t, j, u, R, LNS) is
 // called once per butterfly of the last stage with its R outputs
@@ -114,7 +77,7 @@ __device__ __forceinline__ void tile_stage(float2 (&v)[H * tile_items(L)], float
             for (int i = 0; i < NB; ++i) {
                 const int g = tid + i * NT;
                 const int t = tile_col<LTG, LJ, JF>(g), j = tile_idx<LTG, LJ, JF>(g);
-                const int d = ((j >> LNS) << (LNS + LR)) + (j & ((1 << LNS) - 1));
+                const int d = stage_dest<LNS, LR>(j);
 #pragma unroll
                 for (int r = 0; r < R; ++r) lds[tile_slot<L, LTG, JF>(d + (r << LNS), t)] = v[h * E + i * R + r];
             }
@@ -268,7 +231,7 @@ __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int 
     tile_load<L, LTG, H, false>(v, tid, [&](int t, int j, float2 *u, auto R, auto LJ) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float2 *p = off32(src, (uint32_t(j + (r << LJ)) << l2) + uint32_t(t * H));
+            const float2 *p = off32(src, addr::pass_a_load(uint32_t(j + (r << LJ)), uint32_t(t * H), l2));
             if constexpr (H == 2) {
                 const float4 a = ld4_last(p);
                 u[r] = make_float2(a.x, a.y);
@@ -280,12 +243,11 @@ __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int 
     });
     copy_twiddles(smem, stw, stage_tw_total(L), tid, tile_threads(L, LT, H));
     if (conj_in) tile_conj(v);
-    const uint32_t lbm = (1u << lb) - 1u;
     tile_stage<L, 0, LTG, H, false, PREC>(v, smem + tile_tw(L), smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t k = uint32_t(j + (r << LNS));
-            const uint32_t at = ((k >> lb) << (l2 + lb)) + ((col0 + uint32_t(t * H)) << lb) + (k & lbm);
+            const uint32_t at = addr::pass_a_store(k, col0 + uint32_t(t * H), l2, lb);
 #pragma unroll
             for (int h = 0; h < H; ++h)
                 st2<COH>(reinterpret_cast<char *>(off32(dst, at + (uint32_t(h) << lb))), u[h * E + r]);
@@ -313,7 +275,7 @@ __device__ __forceinline__ void pass_b_tile(const float2 *src, float2 *dst, int 
     tile_load<L, LTG, H, false>(v, tid, [&](int t, int j, float2 *u, auto R, auto LJ) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float2 *p = off32(s, (uint32_t(j + (r << LJ)) << LT) + uint32_t(t * H));
+            const float2 *p = off32(s, addr::pass_b_load(uint32_t(j + (r << LJ)), uint32_t(t * H), LT));
             if constexpr (H == 2) {
                 const float4 a = ld4_last(p);
                 u[r] = make_float2(a.x, a.y);
@@ -324,21 +286,20 @@ __device__ __forceinline__ void pass_b_tile(const float2 *src, float2 *dst, int 
         }
     });
     float2 *cwt = smem + tile_tw(L);  // [r][column]
-    const uint32_t cmask = (16u << l1) - 1u;
     constexpr int CW = 16 << LT;
 #pragma unroll
     for (int i = 0; i < (CW + NT - 1) / NT; ++i) {
         const int e = tid + i * NT;
         if (CW % NT == 0 || e < CW)
-            cwt[e] = T.cw[((col0 + uint32_t(e & ((1 << LT) - 1))) * uint32_t(e >> LT)) & cmask];
+            cwt[e] = T.cw[addr::pass_b_cw(col0 + uint32_t(e & ((1 << LT) - 1)), uint32_t(e >> LT), l1)];
     }
     copy_twiddles(smem, stw, stage_tw_total(L), tid, NT);
     const int t0 = (tid & ((1 << LTG) - 1)) * H, j0 = tid >> LTG;
-    const uint32_t nmask = uint32_t((uint64_t(1) << T.log2N) - 1), lomask = (1u << T.log2Lo) - 1u;
+    const uint32_t lomask = (1u << T.log2Lo) - 1u;
     float2 a[H];
 #pragma unroll
     for (int h = 0; h < H; ++h) {
-        const uint32_t e = ((col0 + uint32_t(t0 + h)) * uint32_t(j0)) & nmask;
+        const uint32_t e = addr::pass_b_top(col0 + uint32_t(t0 + h), uint32_t(j0), T.log2N);
         a[h] = cmul(T.hi[e >> T.log2Lo], T.lo[e & lomask]);
     }
     __syncthreads();
@@ -351,7 +312,7 @@ __device__ __forceinline__ void pass_b_tile(const float2 *src, float2 *dst, int 
     tile_stage<L, 0, LTG, H, false, PREC>(v, cwt, smem, tid, [&](int t, int j, const float2 *u, auto R, auto LNS) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            float2 *p = off32(dst, (uint32_t(j + (r << LNS)) << l1) + uint32_t(t * H));
+            float2 *p = off32(dst, addr::pass_b_store(uint32_t(j + (r << LNS)), uint32_t(t * H), l1));
             const float2 y0 = oscale != 0.f ? conj_scale(u[r], oscale) : u[r];
             if constexpr (H == 2) {
                 const float2 y1 = oscale != 0.f ? conj_scale(u[E + r], oscale) : u[E + r];
