@@ -430,7 +430,8 @@ int queue_count(const paco_batch_options &opt)
 
 // Deals the transforms to the work queues, largest first onto the least loaded
 // (returned queue by queue), and sets which kernel runs them (lw, nq, coh).
-std::vector<std::vector<int32_t>> deal_queues(paco_batch_plan_s *P)
+typedef std::vector<std::vector<int32_t>> Queues;
+Queues deal_queues(paco_batch_plan_s *P)
 {
     using namespace paco;
     int nx = queue_count(P->opt);
@@ -441,7 +442,7 @@ std::vector<std::vector<int32_t>> deal_queues(paco_batch_plan_s *P)
     std::vector<int32_t> order(P->count);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return P->N[a] > P->N[b]; });
-    std::vector<std::vector<int32_t>> qorder;
+    Queues qorder;
     const auto deal = [&](int n) {  // returns the largest queue's items
         std::vector<int64_t> load(n, 0);
         qorder.assign(n, {});
@@ -469,8 +470,9 @@ std::vector<std::vector<int32_t>> deal_queues(paco_batch_plan_s *P)
 }
 
 // Builds jobs, the task order and the device tables of a batch whose
-// per-size plans are fixed.  Returns PACO_OK or an error with the detail set.
-paco_status build_batch(paco_batch_plan_s *P)
+// per-size plans are fixed and whose transforms are dealt (qorder).  Returns
+// PACO_OK or an error with the detail set.
+paco_status build_batch(paco_batch_plan_s *P, const Queues &qorder)
 {
     using namespace paco;
     const int32_t count = P->count;
@@ -497,7 +499,6 @@ paco_status build_batch(paco_batch_plan_s *P)
     int64_t stw_off[kStageMaxLog2 + 1];
     if (!stage_tables(stw, stw_off)) return bfail(PACO_ERR_INVALID_ARG, "internal: stage twiddle layout mismatch");
 
-    const std::vector<std::vector<int32_t>> qorder = deal_queues(P);
     const int nx = P->nq, lw = P->lw ? P->lw : kLogBT;
     const int resident = P->lw ? resident_small(P->lw) : resident_workgroups(P->coh);
     if (resident <= 0) return bfail(PACO_ERR_HIP, "occupancy query failed");
@@ -767,7 +768,7 @@ paco_status tune(const paco_batch_plan_s *P, std::map<int, SizePlan> &plans, con
             T->total = copies << k;
             T->plans[k] = sp;
             if (P->coh) T->opt.flags |= PACO_BATCH_ONE_QUEUE;
-            st = build_batch(T);
+            st = build_batch(T, deal_queues(T));
             float ms = 1e30f;
             for (int rep = 0; st == PACO_OK && rep < 4; ++rep) {
                 e = hipEventRecord(e0, s);
@@ -922,7 +923,7 @@ paco_status paco_batch_plan_create_ex(paco_batch_plan **bp, int32_t count, const
     }
     // per-size plans: cache file (lines of this batch's queue mode), then tuning
     // (unless PACO_BATCH_NO_TUNE), else defaults
-    (void)deal_queues(P);
+    const Queues qorder = deal_queues(P);
     CacheLines lines;
     const std::string key = cache_key();
     if (tune_cache_path) read_cache(tune_cache_path, key, lines);
@@ -946,7 +947,7 @@ paco_status paco_batch_plan_create_ex(paco_batch_plan **bp, int32_t count, const
     } else {
         for (int k : missing) P->plans[k] = paco::candidates(k).front();
     }
-    paco_status st = build_batch(P);
+    paco_status st = build_batch(P, qorder);
     if (st != PACO_OK) {
         free_plan(P);
         return st;
