@@ -4,12 +4,11 @@
 //
 // Work is cut into tasks: up to 2^13 items of whole transforms of one size
 // of at most 2^13 items, a whole transform of 2^14 items, or, for larger
-// ones, one 2^14-item tile of the first or of the second column pass of one
-// transform ("jobs" are the (transform, pass) pairs).  A batch of the first
-// two kinds alone is a plain launch of one workgroup per task.  Otherwise the
-// launch is persistent: a resident workgroup claims the next task number from
-// an atomic ticket counter.  A
-// pass-B task waits until every tile of its transform's pass A is done, on a
+// ones, one tile of the first or of the second column pass of one transform
+// (2^14 items, 2^13 from a shared queue; "jobs" are the (transform, pass)
+// pairs).  A batch of the first two kinds alone is a plain launch of one
+// workgroup per task.  Otherwise the launch is persistent: a resident workgroup
+// claims the next task number from an atomic ticket counter.  A pass-B task waits until every tile of its transform's pass A is done, on a
 // per-job completion counter: the producer writes those tiles, waits for the
 // stores to complete and then increments the counter; the consumer reads the
 // counter and takes a device-scope acquire fence (which also drops stale
@@ -456,7 +455,18 @@ Queues deal_queues(paco_batch_plan_s *P)
     // A queue per XCD keeps a transform's intermediate in that XCD's L2, but
     // a transform then runs on one XCD alone: where the fullest queue would
     // hold more than 1.5 times its share (a few large transforms), all XCDs
-    // serve one queue
+    // serve one queue.  Both sides, us from a queue per XCD / a shared one:
+    //   times its share           2^16          2^18          2^20
+    //   8    (1 transform)     81 / 21      101 / 22      112 / 29
+    //   2.67 (3)               43 / 22       56 / 30       73 / 71
+    //   2    (4)               23 / 23       33 / 32       69 / 83
+    //   1.78 (9)               26 / 28       45 / 70      110 / 95
+    //   1.6  (10)              26 / 29       48 / 74      113 / 122
+    //   1.33 (12)              27 / 31       53 / 78      117 / 153
+    //   1    (8)               25 / 26       38 / 67       87 / 97
+    // 2^20 with 3000 of 2^6 .. 2^12 (1.85) 59 / 45, 2^20 with 16 of 2^18 (1.6) 68 / 92.
+    // At most 1.5 the queues per XCD win throughout, from 2.6 the shared one;
+    // between, neither does, and the line leaves all of it to the shared queue.
     const int kmax = ilog2_pow2(P->N[order[0]]);
     P->lw = kmax <= kShortMaxLog2 ? kLogST : kmax <= kChipMaxLog2 ? kLogBT : 0;
     if (P->lw) nx = 1;

@@ -5,11 +5,11 @@
 // dependent launches took 14.2 us at 2^12, 16.7 at 2^16, 24.2 at 2^20 and 53 at
 // 2^22 (calls back to back), where a copy of the data takes 0.01, 0.2, 3.2 and
 // 13 us.  Lemma 1 holds for any digit-aligned split of N, so the form takes the
-// one with the fewest launches: 5.1, 8.4, 14.7 and 32 us.  One workgroup's
-// kernel takes 4.7 us at 2^12, 6.7 at 2^13 and 11.4 at 2^14, where two passes
-// (3.8 and 4.3 us at 2^15 and 2^16) would be 2 us faster back to back; the batched
-// kernel, which has to give the same bits, moves 5.3 TB/s that way and would
-// move half of it in two passes.
+// one with the fewest launches: 5.1, 8.4, 14.7 and 32 us.  Calls back to back, one
+// workgroup takes 10.2 us at 2^14 (its kernel in a trace 4.5 us at 2^12, 6.6 at
+// 2^13 and 11.2 at 2^14), where the two launches of 2^15 take 7.9: two passes
+// would be 2 us faster there; the batched kernel, which has to give the same bits,
+// moves 5.3 TB/s at 2^14 in one workgroup and would move half of it in two passes.
 #include "direct_kernels.h"
 
 namespace paco {

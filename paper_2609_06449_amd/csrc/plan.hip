@@ -1,6 +1,5 @@
 // C ABI of the PACO library: validation, planning and execution on the
-// caller's stream.  Host code only; the kernels live in local_fft.hip and
-// middle.hip.
+// caller's stream.  Host code only.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>

@@ -476,8 +476,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void s
 // Which accesses are non-temporal.  x is read once and y written once, and
 // what is kept out of the 256 MiB MALL leaves room for the two buffers that
 // the next pass reads; but where those do not fit either, partial reuse
-// decides, so the choices were measured, all 16 of them on 10 shapes, with
-// inputs and outputs that no cache holds (three sets of buffers in turn):
+// decides, and no rule on the size alone gave it: what stands here is the
+// fastest of all 16 choices for each of the 10 shapes, measured with inputs
+// and outputs that no cache holds (three sets of buffers in turn):
 //   pass 1 reads x with last-use loads everywhere; it streams ws (of which
 //   the MALL then holds nothing for pass 2) above 2^26 items only;
 //   pass 3 reads W with last-use loads and streams y at L2 = 256 and in the
@@ -486,10 +487,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void s
 //   L2 = 512, at 2^28 at L2 = 1024.
 // us per transform, against plain accesses but a streamed ws (which had been
 // tuned on one set of buffers, half of it in the MALL): 4096^2 162-166 ->
-// 137, 4096 x 8192 322 -> 280-297, 8192^2 660 -> 607-614, 4096 x 16384 731 ->
+// 132, 4096 x 8192 322 -> 280-297, 8192^2 660 -> 607-614, 4096 x 16384 731 ->
 // 704-709, 16384 x 4096 779 -> 689, 16384^2 2972 -> 2900-2920, 4096 x 32768
 // 1425 -> 1323, 8192 x 32768 2973 -> 2707; 8192 x 16384 and 16384 x 8192 within
-// 3% of 1387 and 1419.  One set of buffers over and over: 4096^2 136.5 -> 134.
+// 3% of 1387 and 1419.  One set of buffers over and over: 4096^2 139 -> 136
+// (pass 1 45 -> 50.5, as it no longer finds part of x in the MALL, pass 2 52 -> 42).
+// 16384^2 is its stage hooks alone: its paco_execute runs 8192 x 32768.
 struct SymTemporal {
     bool stream1, last3, stream3;
     SymTemporal(const SymPass &p, int ll2, int lr2)

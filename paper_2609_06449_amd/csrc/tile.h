@@ -220,7 +220,8 @@ __device__ __forceinline__ void chip14_wide_tile(const float2 *src, float2 *dst,
 // tiles (H = 2) read x and write y with non-temporal accesses: both are used
 // once, and the buffer between the passes then stays in the caches (batch of
 // 4096 transforms 2^8..2^20 3.80 -> 3.63 ms, 128 of 2^20 812 -> 778 us, that
-// is 5.5 TB/s over its two passes, a large copy's rate; 2^23 90 -> 80 us).
+// is 5.5 TB/s over its two passes, a large copy's rate; pass A of 2^23, whose
+// transform takes 72 us, another 7 to 10 us of that).
 template <int L, int LT, int H, bool COH, int PREC = kPrecFP32>
 __device__ __forceinline__ void pass_a_tile(const float2 *src, float2 *dst, int l2, int lb, uint32_t col0,
                                             const float2 *stw, float2 *smem, int tid, bool conj_in)

@@ -128,7 +128,8 @@ PACO_HD int tile_idx(int g)
 // here is its launch and one chain of load, arithmetic, store per workgroup,
 // so the most workgroups win: 4 columns against 8 in both passes took 11.2
 // against 12.1 us at 2^16, 15.6 against 17.0 at 2^20, 34.0 against 39.4 at
-// 2^22 (whole calls, back to back).  Pass times at 2^20: 8.0 and 8.2 us.
+// 2^22 (whole calls, back to back, of that trial; 14.7 and 32 us now).  The two
+// kernels of 2^20 take 7.6 and 8.2 us in a trace, of 2^22 15.7 and 17.2.
 // 4096-point columns (pass A of 2^23 only): 8 columns in two LDS groups, 1024
 // threads and 136 KiB, whose 64-byte runs are read last-use (pass_a_tile).
 // 2^23: 72 us, with 4 columns and two workgroups per CU 79; the three-pass forms
@@ -139,6 +140,7 @@ PACO_HD constexpr int tile_groups(int l) { return l == 12 ? 2 : 1; }
 PACO_HD constexpr int tile_cols(int l, bool mfma) { return l == 12 || (mfma && l == 7) ? 3 : 2; }
 
 // The batched kernel (batch.hip).
+
 // Columns (log2) of a pass tile of 2^l points.  The shared queue serves few
 // large transforms, which a full tile leaves on too few workgroups: half a
 // tile there, 16 items per thread in one group (one transform of 2^16 32 -> 22
