@@ -46,7 +46,8 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "FFT GFLOP/s (5N·log2N/t) + % HBM roofline, N=2^24 c64; MFMA-split vs FP32"
 WORKLOAD = dict(name="2^24 as 4096 x 4096", N1=4096, N2=4096, p=64, b=16, gen="normal", seed=2)
 KERNEL_SOURCES = ["paper_2609_06449_amd/csrc/" + f for f in ("local_fft.hip", "middle.hip", "stages.h", "middle_dev.h",
-                                                                  "paco_internal.h", "split.hip", "sym.hip", "addr.h")]
+                                                                  "paco_internal.h", "split.hip", "sym.hip", "addr.h",
+                                                                  "tile_addr.h")]
 
 
 class HipEvents:

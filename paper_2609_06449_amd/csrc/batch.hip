@@ -464,9 +464,10 @@ Queues deal_queues(paco_batch_plan_s *P)
     //   1.6  (10)              26 / 29       48 / 74      113 / 122
     //   1.33 (12)              27 / 31       53 / 78      117 / 153
     //   1    (8)               25 / 26       38 / 67       87 / 97
-    // 2^20 with 3000 of 2^6 .. 2^12 (1.85) 59 / 45, 2^20 with 16 of 2^18 (1.6) 68 / 92.
-    // At most 1.5 the queues per XCD win throughout, from 2.6 the shared one;
-    // between, neither does, and the line leaves all of it to the shared queue.
+    // 2^20 with 3000 of 2^6 .. 2^12 (1.85) 59 / 45, three of them (1.27) 65 / 50, 2^20
+    // with 16 of 2^18 (1.6) 68 / 92.  Up to 1.5 the queues per XCD win on all but a
+    // few of the lists, above 2 the shared one; between, neither does throughout,
+    // and the line leaves it to the shared queue.
     const int kmax = ilog2_pow2(P->N[order[0]]);
     P->lw = kmax <= kShortMaxLog2 ? kLogST : kmax <= kChipMaxLog2 ? kLogBT : 0;
     if (P->lw) nx = 1;
