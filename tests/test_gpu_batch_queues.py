@@ -38,9 +38,7 @@ def _single_calls(plan, x):
     y, ws, singles = torch.empty_like(x), torch.empty_like(x), {}
     for i, n in enumerate(plan.sizes):
         if n not in singles:
-            N1, N2, p, b = plan.transform_plan(i)
-            # (sizes below 2^4 report N1 or N2 = 1, which no single plan takes: any shape of the size)
-            singles[n] = paco.Plan(N1, N2, 2, 2) if min(N1, N2) >= 2 else paco.Plan(2, n // 2, 2, 2)
+            singles[n] = paco.Plan(*plan.transform_plan(i))
         o = 8 * plan.offsets[i]
         singles[n].execute(x.data_ptr() + o, y.data_ptr() + o, ws.data_ptr() + o, _stream())
     torch.cuda.synchronize()
